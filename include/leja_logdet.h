@@ -96,9 +96,10 @@ typedef struct {
                                 [Q_b | U] into equal column blocks as wide as
                                 the two blocks a step reads and writes allow
                                 within 170 MB and, with the matrix as stored,
-                                within 240 MB (the Infinity Cache), else one
-                                block of at most 64 columns (the gradient's
-                                blocks are always of that kind).  The blocks
+                                within 240 MB (the Infinity Cache), else, and
+                                for a CSR matrix whose columns are scattered
+                                over the rows, one block of at most 64 columns
+                                (the gradient's blocks are always of that kind).  The blocks
                                 set how the quadratic forms' sums are
                                 grouped, hence their last bits              */
     int64_t taylor_cap;      /* max Taylor order of Alg. 1; 0 = 100000000      */

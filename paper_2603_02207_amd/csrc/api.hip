@@ -158,11 +158,20 @@ double stored_bytes(const ld_csr* A, size_t elem, int dia_nd, bool dia_const) {
 // 4: 16.4; 2048^2 GMRF FP32 one 24-column block 47.9, 8: 41.1, 4: 54.6; FP64
 // one block 25.9, 4: 23.9, 2: 32.0; 1024^2 grid FP32 20 columns (a 168 MB
 // pair) 168-175, narrower 125-127.
+//
+// A CSR matrix whose columns are scattered over the rows (kScattered in place
+// of the stored bytes) keeps one block: its gathers miss L2 at any width, so
+// every further block repeats all of them.  Measured (power-law graph, n =
+// 2^20, 64 queries, degree 150, wave-per-row long rows): blocks of 8 columns
+// repeated every gather 9 times, 1552 ms an estimate with the old long rows;
+// one 21-column and one 43-column block take 177 ms.
 constexpr double kBlockPairBudget = 170e6;
+constexpr double kScattered = -1.0;
 
 int choose_block_width(const ld_csr* A, size_t elem, int cols, int user, double stored) {
     const int v = 16 / (int)elem;
     if (user > 0) return std::min(cols, (user + v - 1) / v * v);
+    if (stored == kScattered) return cols;
     const double per_col = 2.0 * (double)A->n * (double)elem;   // block in + block out
     const double room = std::min(kBlockPairBudget, kMallBudget - stored);
     int fit = room > 0 ? (int)(room / per_col) : 0;
@@ -348,16 +357,19 @@ size_t layout_bytes(const EstLayout& L, bool grad) {
 EstLayout layout_envelope(const ld_csr* A, int degree, int n_matvec, bool grad, const ld_options& o) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4;
     EstLayout L = layout_estimate(A, degree, n_matvec, grad, o, matrix_bytes(A, elem));
-    if (grad || o.csr_only || o.block_cols > 0) return L;
+    if (grad || o.block_cols > 0) return L;
+    const auto cover = [&](double stored) {
+        const EstLayout M = layout_estimate(A, degree, n_matvec, false, o, stored);
+        L.yb = std::max(L.yb, M.yb);
+        L.q1b = std::max(L.q1b, M.q1b);
+        L.xb = std::max(L.xb, M.xb);
+        L.W = std::max(L.W, M.W);
+        L.part = std::max(L.part, M.part);
+    };
+    cover(kScattered);
+    if (o.csr_only) return L;
     for (int nd = 1; nd <= kMaxDiag; ++nd)
-        for (bool cst : {false, true}) {
-            const EstLayout M = layout_estimate(A, degree, n_matvec, false, o, stored_bytes(A, elem, nd, cst));
-            L.yb = std::max(L.yb, M.yb);
-            L.q1b = std::max(L.q1b, M.q1b);
-            L.xb = std::max(L.xb, M.xb);
-            L.W = std::max(L.W, M.W);
-            L.part = std::max(L.part, M.part);
-        }
+        for (bool cst : {false, true}) cover(stored_bytes(A, elem, nd, cst));
     return L;
 }
 
@@ -418,6 +430,7 @@ struct LongRows {
     double dia_cval[kMaxDiag] = {};
     int tile_order = LD_TILES_AUTO;   // ld_options.tile_order
     bool skewed = false;              // entries far from even over the eight row bands
+    bool scattered = false;           // most sampled entries lie far from the diagonal
 };
 
 // Chunked XCD bands for stencils (diagonal storage) whose widest diagonal
@@ -518,6 +531,7 @@ int prepare_rows(const ld_csr* A, const ld_options& o, Arena& ar, hipStream_t st
         long long most = 0;
         for (int i = 0; i < kXcds; ++i) most = std::max(most, (long long)h[kBandInfo + i + 1] - h[kBandInfo + i]);
         lr.skewed = (double)most * kXcds > 1.25 * (double)A->nnz;
+        lr.scattered = 2 * h[kFarInfo] > h[kFarInfo + 1];
     }
     if (hcount > 0) {
         lr.list = list;
@@ -874,9 +888,10 @@ int carve(Arena& ar, EstLayout& L, EstimateState& S) {
 // The column blocks for the storage prepare_rows picked, inside the regions
 // of the envelope the workspace was carved with.
 int fit_blocks(const ld_csr* A, int degree, int n_matvec, const ld_options& o, const LongRows& lr, EstLayout& L) {
-    if (o.csr_only || o.block_cols > 0 || lr.dia_nd <= 0) return LD_OK;   // the envelope's own blocks
-    const EstLayout M =
-        layout_estimate(A, degree, n_matvec, false, o, stored_bytes(A, L.elem, lr.dia_nd, lr.dia_pres != nullptr));
+    if (o.block_cols > 0 || (lr.dia_nd <= 0 && !lr.scattered)) return LD_OK;   // the envelope's own blocks
+    const EstLayout M = layout_estimate(
+        A, degree, n_matvec, false, o,
+        lr.dia_nd > 0 ? stored_bytes(A, L.elem, lr.dia_nd, lr.dia_pres != nullptr) : kScattered);
     if (M.yb > L.yb || M.q1b > L.q1b || M.xb > L.xb || M.W > L.W || M.part > L.part)
         return fail(LD_EINVAL, "internal: column blocks outgrow the workspace");
     const auto refit = [](BlkMat& dst, const BlkMat& src) {

@@ -247,13 +247,16 @@ hipError_t launch_narrow(long long len, const double* x, float* y, hipStream_t s
 // Row probe (info: device, 64 ints, preset to 0 by the caller): info[0] =
 // number of diagonals nd (distinct offsets col - row of 64 sampled rows,
 // ascending, in info[1..nd]; -1 if more than kMaxDiag),
-// info[kBandInfo + i] = row_ptr[i*n/8], i = 0..8 (entries per XCD band), and
+// info[kBandInfo + i] = row_ptr[i*n/8], i = 0..8 (entries per XCD band),
+// info[kFarInfo] of info[kFarInfo + 1] entries of the sampled rows (at most 16 a
+// row) lie more than n/16 rows from the diagonal, and
 // at info + kConstInfo nd doubles: each diagonal's value in the first sampled
 // row that stores it.  Then the diagonal storage: dia[r*nd + q] =
 // A[r, r + info[1+q]] or 0, pres[r] bit q = row r stores diagonal q;
 // info[kDiaFlag] = 1 when some stored entry lies on none of the diagonals (the
 // storage is then unusable), info[kConstFlag] = 1 when some entry differs from
 // its diagonal's sampled value (else every diagonal is one constant).
+constexpr int kFarInfo = 10;
 constexpr int kBandInfo = 16;
 constexpr int kConstFlag = 13;
 constexpr int kConstInfo = 32;   // int index; 8-byte aligned doubles

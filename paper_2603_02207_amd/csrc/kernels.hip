@@ -427,12 +427,22 @@ __global__ __launch_bounds__(NT) void step_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Long rows: one workgroup per row (grid-stride over the list).  The row's
-// entries are dealt round-robin to the workgroup's row groups, each group
-// gathers and accumulates its share, and the group sums are added in group
-// order through LDS.  Column sums accumulate over the workgroup's rows and go
-// to partial row part_row0 + blockIdx.x.
+// Long rows: a wave per row, or the whole workgroup for rows above kCoopRow
+// entries.  The row's entries are dealt round-robin to the row groups at work
+// on it, each group gathers and accumulates its share (the next batch's
+// indices are fetched before the current batch's gathers), and the group sums
+// are added by a shuffle tree over the wave (then in wave order through LDS).
+// Workgroup w takes the list positions w, w + grid, ...: neighbouring long
+// rows (the hubs of a power-law graph come first) go to different workgroups.
+// Column sums accumulate over the workgroup's rows and go to partial row
+// part_row0 + blockIdx.x.  Bound by the gathers' latency and the cache lines
+// they touch.  Measured on gfx950 (power-law graph, n = 2^20, 25000 rows of 65
+// to 4100 entries): a workgroup per row with a serial sum over its groups took
+// 840-1090 us per launch at 8 FP32 columns, this form 123 us at 21 columns and
+// 201 us at 43 (5 TB/s of the 64-byte sectors its gathers touch).
 // ---------------------------------------------------------------------------
+constexpr int kCoopRow = 1024;   // entries above which a row takes a whole workgroup
+
 template <typename T, int VEC, int KIND, bool FIRST>
 __global__ __launch_bounds__(256) void long_row_kernel(
     int n, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
@@ -443,127 +453,166 @@ __global__ __launch_bounds__(256) void long_row_kernel(
     const int* __restrict__ count, int part_row0, T* __restrict__ accum, int ldacc, int acc_cols,
     const uint64_t* __restrict__ active) {
     constexpr int NW = 4;
+    constexpr int U = 4;   // entries of a group whose gathers are in flight together
     __shared__ T s_acc[NW * 64 * VEC];
+    __shared__ double s_sum[is_dot(KIND) ? NW * 64 * VEC : 1];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int g = lane / lpr;
     const int li = lane - g * lpr;
     const bool lane_ok = g < rpw;
     const int col = c0 + li * VEC;
-    const int groups = NW * rpw;
-    const int gid = wave * rpw + g;
     const int nlong = *count;
+    int top = 1;   // the tree's first stride, in groups: the largest power of two below rpw
+    while (2 * top < rpw) top *= 2;
     double s0[VEC], s1[VEC], s2[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) s0[e] = s1[e] = s2[e] = 0.0;
-    for (int i = blockIdx.x; i < nlong; i += gridDim.x) {
-        const int row = list[i];
-        const int beg = row_ptr[row], end = row_ptr[row + 1];
-        T acc[VEC];
+
+    // entries beg + first, beg + first + stride, ... of a row, summed over the
+    // wave's groups: group 0 ends with the wave's sum
+    auto gather_row = [&](int beg, int end, int first, int stride, T(&acc)[VEC]) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] = T(0);
         if (lane_ok) {
-            int k = beg + gid;
-            for (; k + 3 * groups < end; k += 4 * groups) {
-                int cc[4];
-                T aa[4];
+            int cn[U];
+            T an[U];
+            auto fetch = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    cc[u] = col_idx[k + u * groups];
-                    aa[u] = val[k + u * groups];
+                for (int u = 0; u < U; ++u) {
+                    const bool on = k + u * stride < end;
+                    cn[u] = on ? col_idx[k + u * stride] : -1;
+                    an[u] = on ? val[k + u * stride] : T(0);
                 }
+            };
+            int k = beg + first;
+            fetch(k);
+            while (k < end) {
+                int cc[U];
+                T aa[U];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const Pack<T, VEC> x = load_pack<T, VEC>(win + (size_t)cc[u] * ld + col);
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[e] = fma(aa[u], x.v[e], acc[e]);
+                for (int u = 0; u < U; ++u) {
+                    cc[u] = cn[u];
+                    aa[u] = an[u];
                 }
-            }
-            for (; k < end; k += groups) {
-                const Pack<T, VEC> x = load_pack<T, VEC>(win + (size_t)col_idx[k] * ld + col);
-                const T a = val[k];
+                k += U * stride;
+                fetch(k);
+                Pack<T, VEC> x[U];
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[e] = fma(a, x.v[e], acc[e]);
+                for (int u = 0; u < U; ++u)
+                    if (cc[u] >= 0) x[u] = load_pack<T, VEC>(win + (size_t)cc[u] * ld + col);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (cc[u] >= 0)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) acc[e] = fma(aa[u], x[u].v[e], acc[e]);
             }
         }
+        for (int h = top; h >= 1; h >>= 1) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const T t = __shfl(acc[e], lane + h * lpr, 64);
+                if (g < h && g + h < rpw) acc[e] += t;
+            }
+        }
+    };
+    // the Newton update of the row, by the lanes of one row group
+    auto finish = [&](int row, const T(&acc)[VEC]) __attribute__((always_inline)) {
+        const Pack<T, VEC> w = load_pack<T, VEC>(win + (size_t)row * ld + col);
+        Pack<T, VEC> o;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o.v[e] = alpha * acc[e] - beta * w.v[e];
+        if constexpr (KIND == STEP_HORNER_SIGNS) {
+            const uint64_t bits = mask[row];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const T sgn = ((bits >> ((col + gshift + e) & 63)) & 1ull) ? T(-1) : T(1);
+                o.v[e] = fma(dj, sgn, o.v[e]);
+            }
+        } else if constexpr (KIND == STEP_HORNER_VEC) {
+            const Pack<T, VEC> v = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) o.v[e] = fma(dj, v.v[e], o.v[e]);
+        } else if constexpr (KIND == STEP_DOT_FWD) {
+            const Pack<T, VEC> x = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (FIRST) s0[e] += (double)x.v[e] * (double)w.v[e];
+                s1[e] += (double)x.v[e] * (double)o.v[e];
+            }
+        } else if constexpr (KIND == STEP_DOT_SQ) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (FIRST) s0[e] += (double)w.v[e] * (double)w.v[e];
+                s1[e] += (double)w.v[e] * (double)o.v[e];
+                s2[e] += (double)o.v[e] * (double)o.v[e];
+            }
+        } else if constexpr (KIND == STEP_ACC_NORM) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) s1[e] += (double)o.v[e] * (double)o.v[e];
+        }
+        if constexpr (KIND == STEP_PLAIN_ACC || KIND == STEP_ACC_NORM) {
+            if (col < acc_cols) {
+                const uint64_t bits = KIND == STEP_ACC_NORM ? *active : ~0ull;
+                T* const pa = accum + (size_t)row * ldacc + col;
+                const Pack<T, VEC> a0 = load_pack<T, VEC>(pa);
+                Pack<T, VEC> a1;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const int b = col - c0 + e;
+                    const bool on = KIND == STEP_PLAIN_ACC || (b < 64 && ((bits >> (b & 63)) & 1ull));
+                    a1.v[e] = on ? fma(dj, o.v[e], a0.v[e]) : a0.v[e];
+                }
+                store_pack<T, VEC>(pa, a1);
+            }
+        }
+        store_pack<T, VEC>(wout + (size_t)row * ld + col, o);
+    };
+
+    T acc[VEC];
+    for (int i = blockIdx.x; i < nlong; i += gridDim.x) {   // rows for the whole workgroup
+        const int row = list[i];
+        const int beg = row_ptr[row], end = row_ptr[row + 1];
+        if (end - beg <= kCoopRow) continue;   // the same for every thread
+        gather_row(beg, end, wave * rpw + g, NW * rpw, acc);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s_acc[threadIdx.x * VEC + e] = acc[e];
         __syncthreads();
         if (wave == 0 && g == 0) {
-            // group sums in group order, then the Newton update of the row
+            for (int wv = 1; wv < NW; ++wv)
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                T t = T(0);
-                for (int q = 0; q < groups; ++q) {
-                    const int wv = q / rpw, gg = q - wv * rpw;
-                    t += s_acc[(wv * 64 + gg * lpr + li) * VEC + e];
-                }
-                acc[e] = t;
-            }
-            const Pack<T, VEC> w = load_pack<T, VEC>(win + (size_t)row * ld + col);
-            Pack<T, VEC> o;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) o.v[e] = alpha * acc[e] - beta * w.v[e];
-            if constexpr (KIND == STEP_HORNER_SIGNS) {
-                const uint64_t bits = mask[row];
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const T sgn = ((bits >> ((col + gshift + e) & 63)) & 1ull) ? T(-1) : T(1);
-                    o.v[e] = fma(dj, sgn, o.v[e]);
-                }
-            } else if constexpr (KIND == STEP_HORNER_VEC) {
-                const Pack<T, VEC> v = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) o.v[e] = fma(dj, v.v[e], o.v[e]);
-            } else if constexpr (KIND == STEP_DOT_FWD) {
-                const Pack<T, VEC> x = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    if (FIRST) s0[e] += (double)x.v[e] * (double)w.v[e];
-                    s1[e] += (double)x.v[e] * (double)o.v[e];
-                }
-            } else if constexpr (KIND == STEP_DOT_SQ) {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    if (FIRST) s0[e] += (double)w.v[e] * (double)w.v[e];
-                    s1[e] += (double)w.v[e] * (double)o.v[e];
-                    s2[e] += (double)o.v[e] * (double)o.v[e];
-                }
-            } else if constexpr (KIND == STEP_ACC_NORM) {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) s1[e] += (double)o.v[e] * (double)o.v[e];
-            }
-            if constexpr (KIND == STEP_PLAIN_ACC || KIND == STEP_ACC_NORM) {
-                if (col < acc_cols) {
-                    const uint64_t bits = KIND == STEP_ACC_NORM ? *active : ~0ull;
-                    T* const pa = accum + (size_t)row * ldacc + col;
-                    const Pack<T, VEC> a0 = load_pack<T, VEC>(pa);
-                    Pack<T, VEC> a1;
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const int b = col - c0 + e;
-                        const bool on = KIND == STEP_PLAIN_ACC || (b < 64 && ((bits >> (b & 63)) & 1ull));
-                        a1.v[e] = on ? fma(dj, o.v[e], a0.v[e]) : a0.v[e];
-                    }
-                    store_pack<T, VEC>(pa, a1);
-                }
-            }
-            store_pack<T, VEC>(wout + (size_t)row * ld + col, o);
+                for (int e = 0; e < VEC; ++e) acc[e] += s_acc[(wv * 64 + li) * VEC + e];
+            finish(row, acc);
         }
         __syncthreads();
     }
-    if constexpr (is_dot(KIND)) {
-        if (wave == 0 && g == 0) {
-            const size_t prow = (size_t)(part_row0 + blockIdx.x) * part_ld + c0 + gshift;
+    for (int i = blockIdx.x + wave * gridDim.x; i < nlong; i += NW * gridDim.x) {   // a wave each
+        const int row = list[i];
+        const int beg = row_ptr[row], end = row_ptr[row + 1];
+        if (end - beg > kCoopRow) continue;   // the same for every lane
+        gather_row(beg, end, g, rpw, acc);
+        if (g == 0) finish(row, acc);
+    }
+    if constexpr (is_dot(KIND)) {   // the waves' sums in wave order
+        const size_t prow = (size_t)(part_row0 + blockIdx.x) * part_ld + c0 + gshift;
+        auto total = [&](const double(&v)[VEC], double* dst) __attribute__((always_inline)) {
+            __syncthreads();
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const int t = li * VEC + e;
-                if (t >= bcols) continue;
-                if (FIRST) ps0[prow + t] = s0[e];
-                ps1[prow + t] = s1[e];
-                if (KIND == STEP_DOT_SQ) ps2[prow + t] = s2[e];
+            for (int e = 0; e < VEC; ++e) s_sum[threadIdx.x * VEC + e] = v[e];
+            __syncthreads();
+            if (wave == 0 && g == 0) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const int t = li * VEC + e;
+                    double a = 0.0;
+                    for (int wv = 0; wv < NW; ++wv) a += s_sum[(wv * 64 + li) * VEC + e];
+                    if (t < bcols) dst[prow + t] = a;
+                }
             }
-        }
+        };
+        if (FIRST) total(s0, ps0);
+        total(s1, ps1);
+        if (KIND == STEP_DOT_SQ) total(s2, ps2);
     }
 }
 
@@ -1970,6 +2019,21 @@ __global__ __launch_bounds__(64) void dia_probe_kernel(int n, const int* __restr
         const int first = __ffsll((unsigned long long)has) - 1;   // at least one lane: u[q] came from a sample
         const double c = __shfl(v, first, 64);
         if (t == 0) cval[q] = c;
+    }
+    // entries far from the diagonal, of at most 16 spread over each sampled row
+    int far = 0, seen = 0;
+    for (int q = 0; q < 16 && q < e - b; ++q) {
+        const int c = col_idx[b + (int)((long long)q * (e - b) / (e - b < 16 ? e - b : 16))];
+        far += abs(c - r) > n / 16;
+        ++seen;
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+        far += __shfl_xor(far, d, 64);
+        seen += __shfl_xor(seen, d, 64);
+    }
+    if (t == 0) {
+        info[kFarInfo] = far;
+        info[kFarInfo + 1] = seen;
     }
     // row_ptr at the boundaries of eight equal row bands (balance of the
     // entries over the XCD bands)
