@@ -117,16 +117,19 @@ typedef struct {
                                 diagonal's entries are all equal; the same sums
                                 in the same order at the same column blocks,
                                 but the default blocks follow the stored bytes
-                                (see block_cols) and the gradient groups its
-                                per-entry sums differently: equal to rounding
-                                there)                                         */
+                                (see block_cols), the gradient groups its
+                                per-entry sums differently, and a constant
+                                five-point stencil with lines of 128 rows or
+                                more takes several Newton steps per launch
+                                (see tile_order): equal to rounding there)    */
     int32_t tile_order;      /* LD_TILES_AUTO / LD_TILES_XCD_BANDS /
                                 LD_TILES_INTERLEAVED: how the workgroups of a
                                 Newton-step launch walk the row tiles (auto:
                                 XCD bands, unless some eighth of the rows holds
                                 more than 1.25x its share of the entries, then
                                 interleaved); the sums' grouping, hence the
-                                last bits of the quadratic forms, depend on it */
+                                last bits of the quadratic forms, depend on it.
+                                Any value but auto keeps one launch per step  */
     int32_t probe_dist;      /* LD_PROBE_RADEMACHER (default) / LD_PROBE_GAUSSIAN:
                                 the distribution of the probe entries of S and
                                 G (Alg. 3 step 2 allows either); ld_logdet_estimate
@@ -147,7 +150,8 @@ typedef struct {
     double sigma, lo, hi;    /* scaling and interval of Q~                     */
     int32_t k, k_G;          /* sketch width and residual probe count          */
     int32_t dot_mode_used;   /* LD_DOT_FORWARD or LD_DOT_SQUARED                */
-    int32_t spmm_launches;   /* recurrence kernel launches                     */
+    int32_t spmm_launches;   /* recurrence kernel launches (a launch may take
+                                several steps, see ld_options.csr_only)        */
     double t_low, t_res;     /* the two traces of Alg. 3 steps 5 and 6         */
     /* Recurrence kernels only, timed with HIP events on `stream` around the
      * back-to-back step launches of each phase: */
@@ -327,8 +331,9 @@ int ld_logdet_estimate_noalloc(const ld_csr* A, double lmin, double lmax, int32_
  * paper).  When the estimate takes the squared basis for its quadratic forms
  * (opts->dot_mode) and k + k_G <= 64, the forward vectors of the estimate's
  * own passes are kept and swept in reverse (the returned estimate is then
- * bit-identical to ld_logdet_estimate's); otherwise one forward pass in the
- * Newton form and one reverse sweep (estimates agree to rounding).  Vectors
+ * bit-identical to ld_logdet_estimate's where that takes one launch per step
+ * and the same column blocks, else equal to rounding); otherwise one forward
+ * pass in the Newton form and one reverse sweep (estimates agree to rounding).  Vectors
  * are kept every opts->ckpt_stride steps (0: all of them while they fit
  * 64 GiB, else the smallest stride that does) and recomputed in between.
  * The quadratic forms' per-entry derivative is symmetric in (r, c) for a

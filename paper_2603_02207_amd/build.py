@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libleja_logdet.so")
-SOURCES = ["host_math.cpp", "kernels.hip", "api.hip"]
+SOURCES = ["host_math.cpp", "kernels.hip", "fused.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "-O3",
@@ -63,7 +63,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(build_dir, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs, jobs = [], []
-    for src in SOURCES:   # the three translation units compile in parallel
+    for src in SOURCES:   # the translation units compile in parallel
         obj = os.path.join(build_dir, os.path.splitext(src)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []
         cmd = [hipcc()] + HIPCC_FLAGS + ident + inc + lang + ["-c", os.path.join(CSRC, src), "-o", obj]

@@ -495,6 +495,91 @@ int run_step(bool f64, const ld_csr* A, StepArgs s, int ncols, int col_block, hi
     return LD_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Several steps per launch (fused.hip): constant five-point stencils with lines
+// of at least kFusedMinWidth rows, unless the caller asks for a tile order
+// (which fixes how each step's own launch walks the rows).  Returns the line
+// length D, or 0.
+// ---------------------------------------------------------------------------
+int fused_line(const ld_csr* A, const LongRows& lr) {
+    if (lr.tile_order != LD_TILES_AUTO || !lr.dia_pres || lr.dia_nd != 5) return 0;
+    const int D = lr.dia_off[4];
+    if (D < kFusedMinWidth || lr.dia_off[0] != -D || lr.dia_off[1] != -1 || lr.dia_off[2] != 0 || lr.dia_off[3] != 1)
+        return 0;
+    return A->n + (long long)(2 * kFusedMax + 4) * D < (1ll << 31) ? D : 0;
+}
+
+// A block as the fused launches address it: rows of a row-major block, or
+// 16-byte column chunks one after another (the work blocks between launches).
+struct FusedBlock {
+    void* p = nullptr;
+    long long cs = 0;
+    int rs = 0;
+    static FusedBlock rows(void* p, int ld, int elem) { return FusedBlock{p, 16 / elem, ld}; }
+    static FusedBlock chunks(void* p, long long n, int elem) { return FusedBlock{p, n * (16 / elem), 16 / elem}; }
+};
+
+// The arguments every fused launch of a block of `cols` columns shares.
+FusedArgs fused_args(const ld_csr* A, const LongRows& lr, const Plan& p, int kind, int steps, int cols, int D) {
+    FusedArgs f{};
+    const bool f64 = A->dtype == LD_F64;
+    f.kind = kind;
+    // the steps go in launches of levels that differ by at most one
+    const int most = fused_levels(kind, f64), launches = (steps + most - 1) / most;
+    f.grid_levels = (steps + launches - 1) / launches;
+    f.n = (int)A->n;
+    f.D = D;
+    f.bcols = cols;
+    f.pres = lr.dia_pres;
+    for (int q = 0; q < 5; ++q) f.cval[q] = lr.dia_cval[q];
+    f.alpha = p.alpha;
+    f.nt_out = alg_bytes_step(A, cols, kind, f64 ? 8 : 4, 5, true) > kMallBudget;   // as run_step
+    return f;
+}
+
+// Levels of the next launch when `left` steps remain (grid_levels or one less).
+int fused_next(const FusedArgs& f, int left) {
+    const int launches = (left + f.grid_levels - 1) / f.grid_levels;
+    return (left + launches - 1) / launches;
+}
+
+void set_in(FusedArgs& f, const FusedBlock& b) {
+    f.win = b.p;
+    f.win_cs = b.cs;
+    f.win_rs = b.rs;
+}
+void set_out(FusedArgs& f, const FusedBlock& b) {
+    f.wout = b.p;
+    f.wout_cs = b.cs;
+    f.wout_rs = b.rs;
+}
+
+// Horner steps m-1 .. 0 over one block from r_m = d_m S (or d_m V): launches of
+// several levels, the last one writing `out`; `d0` stands in for d_0.
+int fused_horner(const ld_csr* A, const LongRows& lr, const Plan& p, FusedArgs f, double d0, const FusedBlock& out,
+                 void* W0, void* W1, hipStream_t st, int* launches) {
+    const bool f64 = A->dtype == LD_F64;
+    const int elem = f64 ? 8 : 4;
+    FusedBlock work[2] = {FusedBlock::chunks(W0, A->n, elem), FusedBlock::chunks(W1, A->n, elem)};
+    int cur = 0;
+    for (int left = p.degree; left > 0;) {
+        f.levels = fused_next(f, left);
+        f.init = left == p.degree;
+        f.init_scale = p.d[p.degree];
+        set_in(f, work[cur]);
+        set_out(f, left == f.levels ? out : work[1 - cur]);
+        for (int t = 0; t < f.levels; ++t) {
+            const int j = left - 1 - t;
+            f.beta[t] = p.beta[j];
+            f.dj[t] = j == 0 ? d0 : p.d[j];
+        }
+        LD_CHECK_HIP(launch_fused(f64, f, st));
+        left -= f.levels;
+        cur = 1 - cur;
+        *launches += 1;
+    }
+    return LD_OK;
+}
 
 // Per-call matrix preparation, with one host sync for all results: the list
 // of rows with more than kLongRow entries, the balance of the entries over
@@ -690,6 +775,26 @@ int sketch_phase(const ld_csr* A, EstimateState& S, hipStream_t st, const VecSto
         // 569 -> 628 us.
         const bool one_plane = (gcol >> 3) == ((gcol + cols - 1) >> 3);
         const int sign_bytes = one_plane && S.planes && S.longrows.dia_nd > 0 ? 1 : 8;
+        if (const int D = keep ? 0 : fused_line(A, S.longrows)) {
+            FusedArgs f = fused_args(A, S.longrows, p, kind, m, cols, D);
+            if (gauss) {
+                void* const sg = S.L.Q1.block(b);
+                LD_CHECK_HIP(launch_gauss_fill(f64, n, cols, S.key0, gcol, 1.0, sg, Blk::plain(S.L.Q1.ld), st));
+                f.vsrc = sg;
+                f.vsrc_cs = 16 / (int)S.L.elem;
+                f.vsrc_rs = S.L.Q1.ld;
+            } else {
+                f.planes = S.planes;
+                f.gcol = gcol;
+            }
+            int launches = 0;
+            LD_CHECK(fused_horner(A, S.longrows, p, f, p.d[0], FusedBlock::rows(Y.block(b), Y.ld, (int)S.L.elem), S.W0,
+                                  S.W1, st, &launches));
+            S.launches1 += launches;
+            // each launch reads and writes the block once (the first reads no block)
+            S.bytes1 += launches * alg_bytes_step(A, cols, kind, S.L.elem, 5, true, 1) - (double)n * cols * S.L.elem;
+            continue;
+        }
         // step j (= m-1 .. 0) writes (j even ? block : W0); r_m sits in the other one
         void* bufs[2] = {Y.block(b), S.W0};
         void* const rm = keep ? keep->at(m) : bufs[(m - 1) % 2 == 0 ? 1 : 0];
@@ -788,6 +893,7 @@ int orthonormalize_and_deflate(const ld_csr* A, uint64_t seed, EstimateState& S,
 int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector<double>& nu_host,
                   const VecStore* keep = nullptr) {
     const bool f64 = A->dtype == LD_F64;
+    const int n = (int)A->n;
     const Plan& p = S.plan;
     const EstLayout& L = S.L;
     const BlkMat& X = L.X;
@@ -800,7 +906,37 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
         const int cols = X.bcols(b), gcol = b * X.bw;
         double* const part = S.part + (size_t)b * nslots * slot_stride;
         int nwg = 0;
-        if (S.mode == LD_DOT_SQUARED) {
+        const int D = keep || S.mode != LD_DOT_SQUARED ? 0 : fused_line(A, S.longrows);
+        FusedArgs f{};
+        FusedGrid grid{};
+        if (D) {
+            f = fused_args(A, S.longrows, p, STEP_DOT_SQ, (m + 1) / 2, cols, D);
+            f.max_parts = L.nwg_dot;
+            grid = fused_grid(n, D, cols, (int)L.elem, f.grid_levels, f.max_parts);
+        }
+        if (D && grid.parts <= L.nwg_dot) {
+            const int h = (m + 1) / 2;
+            FusedBlock work[2] = {FusedBlock::chunks(S.W0, n, (int)L.elem), FusedBlock::chunks(S.W1, n, (int)L.elem)};
+            FusedBlock in = FusedBlock::rows(X.block(b), X.ld, (int)L.elem);
+            f.slot_stride = (long long)slot_stride;
+            f.part_ld = X.bw;
+            int w = 0;
+            for (int a = 0; a < h; a += f.levels) {
+                f.levels = fused_next(f, h - a);
+                f.init = a == 0;
+                set_in(f, in);
+                set_out(f, a + f.levels < h ? work[w] : FusedBlock{});   // the last vector feeds no further step
+                f.part = part + (size_t)(a == 0 ? 0 : 2 * a + 1) * slot_stride;
+                for (int t = 0; t < f.levels; ++t) f.beta[t] = p.beta[a + t];
+                LD_CHECK_HIP(launch_fused(f64, f, st));
+                in = work[w];
+                w = 1 - w;
+                S.launches23 += 1;
+                S.bytes23 += alg_bytes_step(A, cols, STEP_DOT_SQ, L.elem, 5, true);
+            }
+            S.bytes23 -= (double)n * cols * L.elem;   // the last vector is not written
+            nwg = grid.parts;
+        } else if (S.mode == LD_DOT_SQUARED) {
             const int h = (m + 1) / 2;
             // X itself is read once and kept (the gradient needs it); W0/W1 ping-pong
             const void* cur = X.block(b);

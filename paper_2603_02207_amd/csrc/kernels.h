@@ -123,6 +123,76 @@ int step_tile_rows(int bcols, int elem_bytes);
 // long-row launch's kLongWgs).
 hipError_t launch_step(bool f64, const CsrDev& A, const StepArgs& s, hipStream_t st, int* nwg_out = nullptr);
 
+// Several Newton steps per launch on a constant five-point stencil (fused.hip; at
+// least kFusedMinWidth rows a line):
+// diagonals at offsets -D, -1, 0, 1, D (cval in that order, bit q of pres[r] =
+// row r stores diagonal q).  Level t = 0..levels-1 takes w -> alpha*A*w -
+// beta[t]*w (+ dj[t]*S or + dj[t]*V).  Element (r, c) of a block sits at
+// (c / VEC)*cs + r*rs + c % VEC, VEC the elements of 16 bytes: row-major rows
+// (cs = VEC, rs = ld) or 16-byte column chunks one after another (cs = n*VEC,
+// rs = VEC).
+//   STEP_HORNER_SIGNS: S from the byte planes of its sign words (gcol = global
+//                      column of the block's first column); with init the input
+//                      is init_scale*S itself
+//   STEP_HORNER_VEC:   V in vsrc; with init the input is init_scale*V
+//   STEP_DOT_SQ:       level t writes <in,out>, <out,out> of its step to slots
+//                      2t, 2t+1 of part ([slot][partial row][part_ld]); with
+//                      init slot 0 takes <in,in> and the others move up by one.
+//                      wout null: the last vector is not written.
+//
+// Every launch of a phase takes the grid of grid_levels (>= levels), so that all
+// write the same partial rows.
+constexpr int kFusedMax = 6;          // most levels of one launch
+constexpr int kFusedMinWidth = 128;   // shortest lines taken
+constexpr int kFusedWaves = 4096;     // waves a launch aims at: 4 per SIMD
+constexpr int kFusedMinLines = 16;    // fewest lines of a wave (each walks 2*levels more)
+
+// Levels of one launch.  Measured on gfx950, us per step (1024^2 points; 20
+// FP32 / 10 FP64 columns), against the single-step kernels:
+//            levels 1     2     3     4     5     6    single step
+//   SIGNS F32    29.4  15.8  12.3  12.8  12.5  11.6    31
+//         F64    28.8  15.4  11.5  11.2  11.0  10.7    36
+//   VEC   F32    42.6  23.3  17.0  14.2  15.6  16.1    39
+//         F64    41.8  22.9  16.3  13.1  13.3  13.7    39
+//   SQ    F32    30.6  18.4  15.4  20.0  20.3  20.7    35
+//         F64    28.9  16.4  12.1  11.6  14.0  14.8    35
+// More levels move fewer bytes per step but walk more lines and lanes twice;
+// the column sums (16 registers a level) drop the waves per SIMD from 4 to 3
+// above 3 levels in FP32, 4 in FP64.
+constexpr int fused_levels(int kind, bool f64) {
+    return kind == STEP_HORNER_SIGNS ? 6 : kind == STEP_HORNER_VEC ? 4 : f64 ? 4 : 3;
+}
+struct FusedArgs {
+    int kind, levels, grid_levels;
+    bool init;
+    int n, D, bcols;
+    const void* win;
+    long long win_cs;
+    int win_rs;
+    void* wout;
+    long long wout_cs;
+    int wout_rs;
+    const uint16_t* pres;
+    double cval[5];
+    const uint8_t* planes;
+    int gcol;
+    const void* vsrc;
+    long long vsrc_cs;
+    int vsrc_rs;
+    double* part;
+    long long slot_stride;
+    int part_ld;
+    int max_parts;                    // most partial rows (0: no limit)
+    int nt_out;
+    double init_scale, alpha;
+    double beta[kFusedMax], dj[kFusedMax];
+};
+struct FusedGrid {
+    int strips, rows, parts;          // strips of a line, lines of a wave, partial rows
+};
+FusedGrid fused_grid(int n, int D, int bcols, int elem, int levels, int max_parts);
+hipError_t launch_fused(bool f64, const FusedArgs& f, hipStream_t st);
+
 // Sign mask of stream `key`: bit c of word r = (probe(r, c) == -1), c < k <= 64.
 // With `planes` non-null also its eight byte planes: planes[p*n + r] = byte p
 // of word r (8n bytes).
