@@ -113,14 +113,18 @@ int get_workspace(void* ws, size_t ws_bytes, size_t need, OwnedWs& own, Arena& a
     return LD_OK;
 }
 
-int validate_csr(const ld_csr* A, int* dflag, hipStream_t st) {
-    LD_CHECK_HIP(hipMemsetAsync(dflag, 0, sizeof(int), st));
-    LD_CHECK_HIP(launch_validate_csr(dev_of(A), dflag, st));
-    int h = 0;
-    LD_CHECK_HIP(hipMemcpyAsync(&h, dflag, sizeof(int), hipMemcpyDeviceToHost, st));
-    LD_CHECK_HIP(hipStreamSynchronize(st));
-    if (h) return fail(LD_ECSR, "row_ptr/col_idx is not a CSR structure with sorted in-range columns");
+int csr_status(const int* h) {
+    if (h[0] || h[1]) return fail(LD_ECSR, "row_ptr/col_idx is not a CSR structure with sorted in-range columns");
     return LD_OK;
+}
+
+int validate_csr(const ld_csr* A, int* dflag, hipStream_t st) {
+    LD_CHECK_HIP(hipMemsetAsync(dflag, 0, 2 * sizeof(int), st));
+    LD_CHECK_HIP(launch_validate_csr(dev_of(A), dflag, st));
+    int h[2] = {0, 0};
+    LD_CHECK_HIP(hipMemcpyAsync(h, dflag, sizeof(h), hipMemcpyDeviceToHost, st));
+    LD_CHECK_HIP(hipStreamSynchronize(st));
+    return csr_status(h);
 }
 
 // ---------------------------------------------------------------------------
@@ -1704,80 +1708,64 @@ int scratch_address(void** out) {
 // ---------------------------------------------------------------------------
 // Lanczos refinement of the upper end of the spectrum (App. A): `steps`
 // steps of the symmetric Lanczos recurrence in FP64 (an FP32 matrix's values
-// are widened once) from the unit Rademacher vector of generator stream 2
-// (seed 0), no reorthogonalisation; the largest Ritz
+// are widened as they are read) from the unit Rademacher vector of generator
+// stream 2 (seed 0), no reorthogonalisation; the largest Ritz
 // value theta of the tridiagonal projection plus its residual norm
 // beta_k |s_k| (s the Ritz vector in the Krylov basis) and a rounding margin.
 // The Ritz value alone underestimates lambda_max; the residual term is the
 // usual practical upper bound, not a guaranteed one, which is why the caller
-// caps it by Gershgorin's.  Allocates its own vectors.
+// caps it by Gershgorin's.  The scalars stay on the device; the host reads
+// them every kLanczosPoll steps, to stop at an invariant subspace.
 // ---------------------------------------------------------------------------
 constexpr int kMaxLanczos = 512;
+constexpr int kLanczosPoll = 64;
 
-int lanczos_upper(const ld_csr* A_in, int steps, double abs_bound, hipStream_t st, double* out) {
-    const bool f64 = true;
-    const long long n = A_in->n;
-    const size_t elem = 8;
-    const size_t vb = align_up((size_t)n * elem);
-    const size_t pb = align_up((size_t)cross_num_wg((int)n) * sizeof(double));
-    const size_t wb = A_in->dtype == LD_F64 ? 0 : align_up((size_t)A_in->nnz * 8);
-    OwnedWs own;
-    if (hipMalloc(&own.p, 3 * vb + align_up((size_t)n * 8) + pb + 256 + wb) != hipSuccess)
-        return fail(LD_ENOMEM, "hipMalloc failed");
-    char* base = (char*)own.p;
-    ld_csr A64 = *A_in;
-    if (wb) {
-        double* v64 = (double*)(base + 3 * vb + align_up((size_t)n * 8) + pb + 256);
-        LD_CHECK_HIP(launch_widen(A_in->nnz, (const float*)A_in->val, v64, st));
-        A64.val = v64;
-        A64.dtype = LD_F64;
-    }
-    const ld_csr* A = &A64;
-    void* vec[3] = {base, base + vb, base + 2 * vb};     // v_{j-1}, v_j, w
-    uint64_t* mask = (uint64_t*)(base + 3 * vb);
-    double* part = (double*)(base + 3 * vb + align_up((size_t)n * 8));
-    double* scal = (double*)((char*)part + pb);
-    const Blk one = Blk::plain(1);
-    LD_CHECK_HIP(launch_sign_mask((int)n, 1, probe_stream_key(0, 2), mask, st));
-    LD_CHECK_HIP(launch_fill_signs(f64, (int)n, 1, 1, 0, mask, 1.0 / std::sqrt((double)n), vec[1], st));
+size_t lanczos_bytes(long long n) {
+    return 3 * align_up((size_t)n * 8) + align_up((size_t)2 * kLanczosWgs * 8) + align_up((size_t)2 * kMaxLanczos * 8);
+}
+
+int lanczos_upper(const ld_csr* A, int steps, double abs_bound, char* base, hipStream_t st, double* out) {
+    const long long n = A->n;
+    const size_t vb = align_up((size_t)n * 8);
+    double* vec[3] = {(double*)base, (double*)(base + vb), (double*)(base + 2 * vb)};   // u_{j-1}, u_j, w
+    LanczosDev d{};
+    d.wgs = lanczos_wgs((int)n);
+    d.part_a = (double*)(base + 3 * vb);
+    d.part_b = d.part_a + kLanczosWgs;
+    d.alpha = d.part_b + kLanczosWgs;
+    d.beta = d.alpha + kMaxLanczos;
+    LD_CHECK_HIP(launch_lanczos_start((int)n, probe_stream_key(0, 2), 1.0 / std::sqrt((double)n), vec[1], st));
     const int k_max = (int)std::min<long long>(steps, n);
     std::vector<double> a, b;   // diagonal, off-diagonal of the projection
+    std::vector<double> h(2 * kMaxLanczos);
     double beta = 0.0;
-    auto dot = [&](const void* x, const void* y, double* r) -> int {
-        LD_CHECK(cross_product(f64, (int)n, x, one, 1, y, one, 1, nullptr, part, scal, st));
-        LD_CHECK_HIP(hipMemcpyAsync(r, scal, sizeof(double), hipMemcpyDeviceToHost, st));
+    for (int done = 0; done < k_max;) {
+        const int upto = std::min(done + kLanczosPoll, k_max);
+        for (int j = done; j < upto; ++j) {
+            LD_CHECK_HIP(launch_lanczos_step(A->dtype == LD_F64, dev_of(A), d, vec[1], vec[0], vec[2], j, st));
+            std::swap(vec[0], vec[1]);   // u_j becomes u_{j-1}
+            std::swap(vec[1], vec[2]);   // w becomes u_{j+1}; the old u_{j-1} is free
+        }
+        LD_CHECK_HIP(launch_lanczos_beta(d, upto - 1, st));
+        LD_CHECK_HIP(hipMemcpyAsync(h.data(), d.alpha, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
         LD_CHECK_HIP(hipStreamSynchronize(st));
-        return LD_OK;
-    };
-    for (int j = 0; j < k_max; ++j) {
-        StepArgs s{};
-        s.kind = STEP_PLAIN;
-        s.win = vec[1];
-        s.wout = vec[2];
-        s.ld = 1;
-        s.alpha = 1.0;
-        s.beta = 0.0;
-        LD_CHECK(run_step(f64, A, s, 1, 1, st, nullptr, LongRows{}));      // w = A v_j
-        double alpha = 0.0;
-        LD_CHECK(dot(vec[1], vec[2], &alpha));
-        LD_CHECK_HIP(launch_axpby(f64, n, -alpha, vec[1], 1.0, vec[2], st));
-        if (j > 0) LD_CHECK_HIP(launch_axpby(f64, n, -beta, vec[0], 1.0, vec[2], st));
-        a.push_back(alpha);
-        double bb = 0.0;
-        LD_CHECK(dot(vec[2], vec[2], &bb));
-        beta = std::sqrt(std::fmax(bb, 0.0));
-        if (!std::isfinite(alpha) || !std::isfinite(beta))
-            return fail(LD_EINVAL, "non-finite value in the Lanczos recurrence (non-finite entries of A?)");
-        if (j + 1 == k_max || beta <= 1e-14 * std::fmax(std::fabs(alpha), abs_bound)) break;   // done / invariant subspace
-        b.push_back(beta);
-        // v_{j+1} = w / beta into the buffer of v_{j-1}; then rotate
-        LD_CHECK_HIP(launch_scale_copy(f64, (int)n, 1, vec[2], 1, 1.0 / beta, vec[0], 1, st));
-        std::swap(vec[0], vec[1]);   // vec[1] = v_{j+1}, vec[0] = v_j
+        for (int j = done; j < upto; ++j) {
+            const double alpha = h[j];
+            beta = h[kMaxLanczos + j];
+            a.push_back(alpha);
+            if (!std::isfinite(alpha) || !std::isfinite(beta))
+                return fail(LD_EINVAL, "non-finite value in the Lanczos recurrence (non-finite entries of A?)");
+            if (j + 1 == k_max || beta <= 1e-14 * std::fmax(std::fabs(alpha), abs_bound)) {   // done / invariant subspace
+                done = k_max;
+                break;
+            }
+            b.push_back(beta);
+        }
+        if (done < k_max) done = upto;
     }
     double theta = 0.0, last = 0.0;
     tridiag_top_eigenpair(a, b, &theta, &last);
     *out = theta + beta * std::fabs(last) + 8.0 * 0x1p-53 * abs_bound * std::sqrt((double)a.size());
-    LD_CHECK_HIP(hipStreamSynchronize(st));
     return LD_OK;
 }
 
@@ -2192,26 +2180,28 @@ int ld_spectral_bounds(const ld_csr* A, int32_t lanczos_steps, void* stream, dou
         return fail(LD_EINVAL, "need lmin, lmax non-null and 0 <= lanczos_steps <= " +
                                    std::to_string(kMaxLanczos));
     hipStream_t st = (hipStream_t)stream;
-    const int nwg = gersh_num_wg((int)A->n);
+    // flags, the two bounds, Gershgorin's partials (then the Lanczos vectors in their place)
+    const size_t gersh = align_up((size_t)2 * gersh_num_wg((int)A->n) * sizeof(double));
     OwnedWs own;
-    if (hipMalloc(&own.p, (size_t)2 * nwg * sizeof(double) + 256) != hipSuccess)
+    if (hipMalloc(&own.p, kAlign + std::max(gersh, lanczos_steps > 0 ? lanczos_bytes(A->n) : 0)) != hipSuccess)
         return fail(LD_ENOMEM, "hipMalloc failed");
-    int* flag = (int*)((char*)own.p + (size_t)2 * nwg * sizeof(double));
-    LD_CHECK(validate_csr(A, flag, st));
-    LD_CHECK_HIP(launch_gershgorin(A->dtype == LD_F64, dev_of(A), (double*)own.p, st));
-    std::vector<double> h((size_t)2 * nwg);
-    LD_CHECK_HIP(hipMemcpyAsync(h.data(), own.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+    char* const base = (char*)own.p;
+    LD_CHECK_HIP(hipMemsetAsync(base, 0, 16, st));
+    LD_CHECK_HIP(launch_validate_csr(dev_of(A), (int*)base, st));
+    LD_CHECK_HIP(launch_gershgorin(A->dtype == LD_F64, dev_of(A), (double*)(base + kAlign), (double*)(base + 16), st));
+    struct {
+        int flag[4];
+        double lo, hi;
+    } h;
+    LD_CHECK_HIP(hipMemcpyAsync(&h, base, sizeof(h), hipMemcpyDeviceToHost, st));
     LD_CHECK_HIP(hipStreamSynchronize(st));
-    double lo = INFINITY, hi = -INFINITY;
-    for (int i = 0; i < nwg; ++i) {
-        lo = std::fmin(lo, h[2 * i]);
-        hi = std::fmax(hi, h[2 * i + 1]);
-    }
+    LD_CHECK(csr_status(h.flag));
+    const double lo = h.lo, hi = h.hi;
     *lmin = lo;
     *lmax = hi;
-    if (lanczos_steps > 0 && A->n > 0) {
+    if (lanczos_steps > 0) {
         double top = hi;
-        LD_CHECK(lanczos_upper(A, lanczos_steps, std::fmax(std::fabs(lo), std::fabs(hi)), st, &top));
+        LD_CHECK(lanczos_upper(A, lanczos_steps, std::fmax(std::fabs(lo), std::fabs(hi)), base + kAlign, st, &top));
         *lmax = std::fmin(hi, top);
     }
     if (!(lo > 0.0)) return fail(LD_EINDEF, "Gershgorin lower bound is not positive");

@@ -241,55 +241,54 @@ uint64_t probe_stream_key(uint64_t seed, int stream) {
     return splitmix_mix(seed + (uint64_t)(stream + 1) * 0x9E3779B97F4A7C15ull);
 }
 
-void tridiag_top_eigenpair(const std::vector<double>& a, const std::vector<double>& b, double* theta,
+// Implicit-shift QR on the tridiagonal matrix (Golub & Van Loan, Matrix
+// Computations, sec. 8.3): each sweep chases the bulge of one Wilkinson shift
+// down an unreduced block by Givens rotations of neighbouring rows and columns;
+// of the eigenvectors only the last components are carried along (a row of the
+// accumulated rotations).  O(k) per sweep, about two sweeps per eigenvalue (64
+// rows: 0.1 ms, where cyclic Jacobi on the dense matrix took 25 ms).
+void tridiag_top_eigenpair(const std::vector<double>& a_in, const std::vector<double>& b_in, double* theta,
                            double* last) {
-    const int k = (int)a.size();
-    std::vector<double> M((size_t)k * k, 0.0), V((size_t)k * k, 0.0);
-    for (int i = 0; i < k; ++i) {
-        M[(size_t)i * k + i] = a[i];
-        V[(size_t)i * k + i] = 1.0;
-        if (i + 1 < k) M[(size_t)i * k + i + 1] = M[(size_t)(i + 1) * k + i] = b[i];
-    }
-    // cyclic Jacobi: rotate away each off-diagonal entry in turn until the
-    // off-diagonal mass is negligible against the diagonal
-    for (int sweep = 0; sweep < 100; ++sweep) {
-        double off = 0.0, dia = 0.0;
-        for (int i = 0; i < k; ++i)
-            for (int j = 0; j < k; ++j) {
-                const double x = M[(size_t)i * k + j];
-                (i == j ? dia : off) += x * x;
+    const int k = (int)a_in.size();
+    std::vector<double> a = a_in, b(b_in.begin(), b_in.begin() + std::max(0, k - 1)), z((size_t)k, 0.0);
+    b.push_back(0.0);
+    z[(size_t)k - 1] = 1.0;
+    const auto negligible = [&](int i) {   // the coupling of rows i, i+1
+        return std::fabs(b[i]) <= 0x1p-53 * (std::fabs(a[i]) + std::fabs(a[i + 1]));
+    };
+    for (int q = k - 1, sweeps = 0; q > 0 && sweeps < 60 * k;) {
+        if (negligible(q - 1)) {
+            b[q - 1] = 0.0;
+            --q;
+            continue;
+        }
+        int p = q - 1;   // the unreduced block p..q
+        while (p > 0 && !negligible(p - 1)) --p;
+        ++sweeps;
+        const double d = 0.5 * (a[q - 1] - a[q]), r = std::hypot(d, b[q - 1]);
+        const double mu = a[q] - b[q - 1] * (b[q - 1] / (d + (d >= 0.0 ? r : -r)));
+        double x = a[p] - mu, y = b[p];
+        for (int i = p; i < q; ++i) {
+            const double h = std::hypot(x, y);
+            const double c = h == 0.0 ? 1.0 : x / h, s = h == 0.0 ? 0.0 : y / h;
+            if (i > p) b[i - 1] = h;
+            const double ai = a[i], an = a[i + 1], bi = b[i];
+            a[i] = c * c * ai + 2.0 * c * s * bi + s * s * an;
+            a[i + 1] = s * s * ai - 2.0 * c * s * bi + c * c * an;
+            b[i] = c * s * (an - ai) + (c * c - s * s) * bi;
+            const double zi = z[i], zn = z[i + 1];
+            z[i] = c * zi + s * zn;
+            z[i + 1] = c * zn - s * zi;
+            if (i + 1 < q) {
+                x = b[i];
+                y = s * b[i + 1];
+                b[i + 1] = c * b[i + 1];
             }
-        if (off <= 1e-32 * dia || off == 0.0) break;
-        for (int p = 0; p < k; ++p)
-            for (int q = p + 1; q < k; ++q) {
-                const double apq = M[(size_t)p * k + q];
-                if (apq == 0.0) continue;
-                const double app = M[(size_t)p * k + p], aqq = M[(size_t)q * k + q];
-                const double tau = (aqq - app) / (2.0 * apq);
-                const double t = (tau >= 0 ? 1.0 : -1.0) / (std::fabs(tau) + std::sqrt(1.0 + tau * tau));
-                const double c = 1.0 / std::sqrt(1.0 + t * t), s = t * c;
-                for (int r = 0; r < k; ++r) {   // M <- M J (columns p, q)
-                    const double mp = M[(size_t)r * k + p], mq = M[(size_t)r * k + q];
-                    M[(size_t)r * k + p] = c * mp - s * mq;
-                    M[(size_t)r * k + q] = s * mp + c * mq;
-                }
-                for (int r = 0; r < k; ++r) {   // M <- J^T M (rows p, q)
-                    const double mp = M[(size_t)p * k + r], mq = M[(size_t)q * k + r];
-                    M[(size_t)p * k + r] = c * mp - s * mq;
-                    M[(size_t)q * k + r] = s * mp + c * mq;
-                }
-                for (int r = 0; r < k; ++r) {   // V <- V J
-                    const double vp = V[(size_t)r * k + p], vq = V[(size_t)r * k + q];
-                    V[(size_t)r * k + p] = c * vp - s * vq;
-                    V[(size_t)r * k + q] = s * vp + c * vq;
-                }
-            }
+        }
     }
-    int top = 0;
-    for (int i = 1; i < k; ++i)
-        if (M[(size_t)i * k + i] > M[(size_t)top * k + top]) top = i;
-    *theta = M[(size_t)top * k + top];
-    *last = V[(size_t)(k - 1) * k + top];   // column `top` of V is the eigenvector
+    const int top = (int)(std::max_element(a.begin(), a.end()) - a.begin());
+    *theta = a[top];
+    *last = z[top];
 }
 
 void KahanSum::add(double x) {

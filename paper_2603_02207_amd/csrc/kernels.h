@@ -239,12 +239,15 @@ hipError_t launch_rowmat(bool f64, int n, const void* Y, Blk by, int ky, const d
                          double sign_m, const uint64_t* zmask, const void* base, Blk bb,
                          void* out, Blk bo, hipStream_t st);
 
-// CSR structure check: *flag (device int) set to 1 on any violation.
+// CSR structure check: flag[0], flag[1] (device ints, preset to 0) both stay 0
+// unless there is a violation.
 hipError_t launch_validate_csr(const CsrDev& A, int* flag, hipStream_t st);
 
-// Gershgorin: per-workgroup (min(a_ii - r_i), max(a_ii + r_i)) into part[2*wg].
+// Gershgorin: (min(a_ii - r_i), max(a_ii + r_i)) into out[0..2); part: 2 *
+// gersh_num_wg(n) doubles.  Reads nothing out of range whatever the CSR arrays
+// hold (the result then means nothing).
 int gersh_num_wg(int n);
-hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, hipStream_t st);
+hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, double* out, hipStream_t st);
 
 // Gradient sweep step (all blocks n x ld row-major, ncols used; grad FP64):
 //   grad[nz(r,c)] (+)= alpha * sum_cols own[r, col] * w[c, col]
@@ -340,11 +343,20 @@ hipError_t launch_dia_build(bool f64, const CsrDev& A, void* dia, uint16_t* pres
 hipError_t launch_adapt_decide(const double* sums, int stride, int qc, double dm_abs, double tol, int m,
                                uint64_t* mask, int* deg, hipStream_t st);
 
-// y[i] = (double)x[i], i < len.
-hipError_t launch_widen(long long len, const float* x, double* y, hipStream_t st);
-
-// y = a*x + b*y elementwise on contiguous arrays of length len.
-hipError_t launch_axpby(bool f64, long long len, double a, const void* x, double b, void* y,
-                        hipStream_t st);
+// Lanczos recurrence (lanczos.hip): step j of the FP64 recurrence on A, u = u_j,
+// u_prev = u_{j-1}, w becomes u_{j+1} (all unnormalised); alpha[j], and beta of
+// the step before, are written on the device.  launch_lanczos_beta writes
+// beta[j] after step j.
+constexpr int kLanczosWgs = 2048;
+struct LanczosDev {
+    int wgs;                      // lanczos_wgs(n): partial sums of part_a, part_b
+    double *part_a, *part_b;
+    double *alpha, *beta;
+};
+int lanczos_wgs(int n);
+hipError_t launch_lanczos_start(int n, uint64_t key, double scale, double* u, hipStream_t st);
+hipError_t launch_lanczos_step(bool f64, const CsrDev& A, const LanczosDev& d, const double* u, const double* u_prev,
+                               double* w, int j, hipStream_t st);
+hipError_t launch_lanczos_beta(const LanczosDev& d, int j, hipStream_t st);
 
 }  // namespace ld

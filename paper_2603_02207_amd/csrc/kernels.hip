@@ -1866,34 +1866,56 @@ hipError_t launch_rowmat(bool f64, int n, const void* Y, Blk by, int ky, const d
 }
 
 // ---------------------------------------------------------------------------
-// CSR structure check (reads col_idx only inside [0, nnz))
+// CSR structure check (reads col_idx only inside [0, nnz)).  A thread per entry:
+// columns in range, and the positions k whose column is not above the one before
+// are counted; a thread per row: row pointers, and the row starts among those
+// positions are counted off.  The columns are sorted inside every row exactly
+// when nothing is left (flag[1] = 0).  A thread per row alone took 1.8 ms on a
+// power-law graph of 17M entries (rows of 4100), this form 58 us.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void validate_kernel(int n, int nnz,
                                                             const int* __restrict__ row_ptr,
                                                             const int* __restrict__ col_idx,
                                                             int* __restrict__ flag) {
-    const int r = blockIdx.x * kThreads + threadIdx.x;
-    if (r >= n) return;
-    const int b = row_ptr[r], e = row_ptr[r + 1];
-    bool bad = (b < 0) || (e < b) || (e > nnz) || (r == 0 && b != 0) || (r == n - 1 && e != nnz);
-    if (!bad) {
-        int prev = -1;
-        for (int k = b; k < e; ++k) {
-            const int c = col_idx[k];
-            if (c < 0 || c >= n || c <= prev) {
-                bad = true;
-                break;
-            }
-            prev = c;
-        }
+    const long long step = (long long)gridDim.x * kThreads, first = (long long)blockIdx.x * kThreads + threadIdx.x;
+    int bad = 0, drops = 0;
+#pragma unroll 4
+    for (long long i = first; i < nnz; i += step) {
+        const int c = col_idx[i], before = col_idx[i > 0 ? i - 1 : 0];
+        bad |= c < 0 || c >= n;
+        drops += i > 0 && c <= before;
     }
-    if (bad) *flag = 1;
+#pragma unroll 2
+    for (long long i = first; i < n; i += step) {
+        const int b = row_ptr[i], e = row_ptr[i + 1];
+        const bool off = b < 0 || e < b || e > nnz || (i == 0 && b != 0) || (i == n - 1 && e != nnz);
+        bad |= off;
+        if (!off && b > 0 && b < e) drops -= col_idx[b] <= col_idx[b - 1];
+    }
+    for (int h = 32; h >= 1; h >>= 1) drops += __shfl_xor(drops, h, 64);
+    __shared__ int s_drops[kWaves], s_bad[kWaves];
+    const int any = __any(bad);
+    if ((threadIdx.x & 63) == 0) {
+        s_drops[threadIdx.x >> 6] = drops;
+        s_bad[threadIdx.x >> 6] = any;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {   // one atomic per workgroup: an integer count, any order
+        int d = 0, f = 0;
+        for (int wv = 0; wv < kWaves; ++wv) {
+            d += s_drops[wv];
+            f |= s_bad[wv];
+        }
+        if (f) flag[0] = 1;
+        if (d != 0) atomicAdd(&flag[1], d);
+    }
 }
 
 hipError_t launch_validate_csr(const CsrDev& A, int* flag, hipStream_t st) {
     if (A.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(validate_kernel, dim3(div_up(A.n, kThreads)), dim3(kThreads), 0, st, A.n,
-                       A.nnz, A.row_ptr, A.col_idx, flag);
+    // 16 entries a thread: one atomic per workgroup costs more than the reads of a small matrix
+    const int nb = std::min(std::max(div_up(std::max(A.n, A.nnz), kThreads * 16), 1), 1024);
+    hipLaunchKernelGGL(validate_kernel, dim3(nb), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr, A.col_idx, flag);
     return hipGetLastError();
 }
 
@@ -1901,7 +1923,7 @@ hipError_t launch_validate_csr(const CsrDev& A, int* flag, hipStream_t st) {
 // Gershgorin discs
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(kThreads) void gersh_kernel(int n, const int* __restrict__ row_ptr,
+__global__ __launch_bounds__(kThreads) void gersh_kernel(int n, int nnz, const int* __restrict__ row_ptr,
                                                          const int* __restrict__ col_idx,
                                                          const T* __restrict__ val,
                                                          double* __restrict__ part) {
@@ -1909,7 +1931,8 @@ __global__ __launch_bounds__(kThreads) void gersh_kernel(int n, const int* __res
     double lo = __builtin_inf(), hi = -__builtin_inf();
     if (r < n) {
         double diag = 0.0, rad = 0.0;
-        for (int k = row_ptr[r]; k < row_ptr[r + 1]; ++k) {
+        const int end = min(row_ptr[r + 1], nnz);
+        for (int k = max(row_ptr[r], 0); k < end; ++k) {
             const double v = (double)val[k];
             if (col_idx[k] == r)
                 diag += v;
@@ -1938,26 +1961,42 @@ __global__ __launch_bounds__(kThreads) void gersh_kernel(int n, const int* __res
 
 int gersh_num_wg(int n) { return div_up(n, kThreads); }
 
-hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, hipStream_t st) {
+// the workgroups' discs to one (minimum and maximum: any order)
+__global__ __launch_bounds__(kThreads) void gersh_total_kernel(int wgs, const double* __restrict__ part,
+                                                               double* __restrict__ out) {
+    __shared__ double slo[kThreads], shi[kThreads];
+    double lo = __builtin_inf(), hi = -__builtin_inf();
+    for (int i = threadIdx.x; i < wgs; i += kThreads) {
+        lo = fmin(lo, part[2 * i]);
+        hi = fmax(hi, part[2 * i + 1]);
+    }
+    slo[threadIdx.x] = lo;
+    shi[threadIdx.x] = hi;
+    __syncthreads();
+    for (int s = kThreads / 2; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            slo[threadIdx.x] = fmin(slo[threadIdx.x], slo[threadIdx.x + s]);
+            shi[threadIdx.x] = fmax(shi[threadIdx.x], shi[threadIdx.x + s]);
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        out[0] = slo[0];
+        out[1] = shi[0];
+    }
+}
+
+hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, double* out, hipStream_t st) {
     const int nwg = gersh_num_wg(A.n);
     if (nwg == 0) return hipSuccess;
     if (f64)
-        hipLaunchKernelGGL(gersh_kernel<double>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.row_ptr,
+        hipLaunchKernelGGL(gersh_kernel<double>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr,
                            A.col_idx, (const double*)A.val, part);
     else
-        hipLaunchKernelGGL(gersh_kernel<float>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.row_ptr,
+        hipLaunchKernelGGL(gersh_kernel<float>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr,
                            A.col_idx, (const float*)A.val, part);
+    hipLaunchKernelGGL(gersh_total_kernel, dim3(1), dim3(kThreads), 0, st, nwg, part, out);
     return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// elementwise y = a x + b y
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kThreads) void axpby_kernel(long long len, T a, const T* __restrict__ x,
-                                                         T b, T* __restrict__ y) {
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i < len) y[i] = a * x[i] + b * y[i];
 }
 
 // Candidate diagonals: the distinct offsets col - row of 64 rows scattered
@@ -2142,31 +2181,6 @@ hipError_t launch_adapt_decide(const double* sums, int stride, int qc, double dm
     if (qc < 1 || qc > 64) return hipErrorInvalidValue;
     hipLaunchKernelGGL(adapt_decide_kernel, dim3(1), dim3(64), 0, st, sums, stride, qc, dm_abs, tol, m, mask,
                        deg);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(kThreads) void widen_kernel(long long len, const float* __restrict__ x,
-                                                         double* __restrict__ y) {
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i < len) y[i] = (double)x[i];
-}
-
-hipError_t launch_widen(long long len, const float* x, double* y, hipStream_t st) {
-    if (len == 0) return hipSuccess;
-    hipLaunchKernelGGL(widen_kernel, dim3(div_up(len, kThreads)), dim3(kThreads), 0, st, len, x, y);
-    return hipGetLastError();
-}
-
-hipError_t launch_axpby(bool f64, long long len, double a, const void* x, double b, void* y,
-                        hipStream_t st) {
-    if (len == 0) return hipSuccess;
-    const int nb = div_up(len, kThreads);
-    if (f64)
-        hipLaunchKernelGGL(axpby_kernel<double>, dim3(nb), dim3(kThreads), 0, st, len, a,
-                           (const double*)x, b, (double*)y);
-    else
-        hipLaunchKernelGGL(axpby_kernel<float>, dim3(nb), dim3(kThreads), 0, st, len, (float)a,
-                           (const float*)x, (float)b, (float*)y);
     return hipGetLastError();
 }
 

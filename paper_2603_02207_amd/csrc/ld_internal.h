@@ -32,7 +32,7 @@ uint64_t splitmix_mix(uint64_t z);
 uint64_t probe_stream_key(uint64_t seed, int stream);
 
 // Largest eigenvalue of the symmetric tridiagonal matrix with diagonal a[0..k)
-// and off-diagonal b[0..k-1) (cyclic Jacobi on the dense k x k matrix), and
+// and off-diagonal b[0..k-1) (implicit-shift QR), and
 // the last component of its unit eigenvector.
 void tridiag_top_eigenpair(const std::vector<double>& a, const std::vector<double>& b, double* theta,
                            double* last);
