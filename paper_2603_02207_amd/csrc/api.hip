@@ -523,8 +523,50 @@ struct FusedBlock {
     static FusedBlock chunks(void* p, long long n, int elem) { return FusedBlock{p, n * (16 / elem), 16 / elem}; }
 };
 
+// Coefficients of the fused launches: w -> off . neighbours + mid_j w, off =
+// alpha times the off-diagonal values, mid_j = alpha times the centre's - beta_j.
+// Rounded to FP32, each would be the same error in every row (up to 2^-24 of A),
+// larger than the single steps' own.  So the basis is moved to where they round
+// to themselves: the variable f T in place of T, f within 2^-24 of 1, makes alpha
+// off an FP32 number, and the centres xi_j within 2^-23 of theirs make every
+// mid_j one.  The polynomial's coefficients follow in FP64 (d by f^-j and
+// shift_centres; the squared basis is then formed at these centres).  Emulated
+// and measured on 100^2 to 400^2 grids: log(A) V 1.0-1.3e-7 off in FP32, single
+// steps 1.1-1.7e-7, plain folding 1.6-2.1e-7.
+struct FusedPlan {
+    double alpha = 0.0;
+    std::vector<double> xi, d, mid, nbeta;   // nbeta_j = mid_j without the centre's entry
+};
+
+FusedPlan fused_plan(const ld_csr* A, const LongRows& lr, const Plan& p) {
+    FusedPlan q;
+    const int m = p.degree;
+    const bool f64 = A->dtype == LD_F64;
+    const double off = p.alpha * lr.dia_cval[4];
+    const double f = f64 || !std::isnormal((float)off) ? 1.0 : (double)(float)off / off;
+    q.alpha = p.alpha * f;
+    q.xi.resize((size_t)m);
+    q.d = p.d;
+    q.mid.resize((size_t)m);
+    q.nbeta.resize((size_t)m);
+    const double centre = q.alpha * lr.dia_cval[2];
+    std::vector<double> to((size_t)m);
+    double fj = 1.0;
+    for (int j = 0; j < m; ++j) {
+        q.xi[j] = f * p.xi[j];
+        fj /= f;
+        q.d[j + 1] *= fj;
+        const double mid = centre - f * p.beta[j];
+        q.mid[j] = f64 ? mid : (double)(float)mid;
+        q.nbeta[j] = q.mid[j] - centre;
+        to[j] = q.xi[j] + (mid - q.mid[j]);
+    }
+    shift_centres(q.xi, to, q.d);
+    return q;
+}
+
 // The arguments every fused launch of a block of `cols` columns shares.
-FusedArgs fused_args(const ld_csr* A, const LongRows& lr, const Plan& p, int kind, int steps, int cols, int D) {
+FusedArgs fused_args(const ld_csr* A, const LongRows& lr, const FusedPlan& q, int kind, int steps, int cols, int D) {
     FusedArgs f{};
     const bool f64 = A->dtype == LD_F64;
     f.kind = kind;
@@ -535,8 +577,7 @@ FusedArgs fused_args(const ld_csr* A, const LongRows& lr, const Plan& p, int kin
     f.D = D;
     f.bcols = cols;
     f.pres = lr.dia_pres;
-    for (int q = 0; q < 5; ++q) f.cval[q] = lr.dia_cval[q];
-    f.alpha = p.alpha;
+    for (int t = 0; t < 5; ++t) f.off[t] = q.alpha * lr.dia_cval[t];
     f.nt_out = alg_bytes_step(A, cols, kind, f64 ? 8 : 4, 5, true) > kMallBudget;   // as run_step
     return f;
 }
@@ -559,23 +600,25 @@ void set_out(FusedArgs& f, const FusedBlock& b) {
 }
 
 // Horner steps m-1 .. 0 over one block from r_m = d_m S (or d_m V): launches of
-// several levels, the last one writing `out`; `d0` stands in for d_0.
-int fused_horner(const ld_csr* A, const LongRows& lr, const Plan& p, FusedArgs f, double d0, const FusedBlock& out,
+// several levels, the last one writing `out`; `add` is added to d_0.
+int fused_horner(const ld_csr* A, const FusedPlan& q, FusedArgs f, double add, const FusedBlock& out,
                  void* W0, void* W1, hipStream_t st, int* launches) {
     const bool f64 = A->dtype == LD_F64;
     const int elem = f64 ? 8 : 4;
     FusedBlock work[2] = {FusedBlock::chunks(W0, A->n, elem), FusedBlock::chunks(W1, A->n, elem)};
+    const int m = (int)q.mid.size();
     int cur = 0;
-    for (int left = p.degree; left > 0;) {
+    for (int left = m; left > 0;) {
         f.levels = fused_next(f, left);
-        f.init = left == p.degree;
-        f.init_scale = p.d[p.degree];
+        f.init = left == m;
+        f.init_scale = q.d[m];
         set_in(f, work[cur]);
         set_out(f, left == f.levels ? out : work[1 - cur]);
         for (int t = 0; t < f.levels; ++t) {
             const int j = left - 1 - t;
-            f.beta[t] = p.beta[j];
-            f.dj[t] = j == 0 ? d0 : p.d[j];
+            f.mid[t] = q.mid[j];
+            f.nbeta[t] = q.nbeta[j];
+            f.dj[t] = q.d[j] + (j == 0 ? add : 0.0);
         }
         LD_CHECK_HIP(launch_fused(f64, f, st));
         left -= f.levels;
@@ -679,6 +722,8 @@ struct EstimateState {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};   // step-phase brackets
     bool timed = true;              // false: no HIP events (ld_logdet_estimate_noalloc)
     LongRows longrows;
+    int fused_D = 0;                // line length where several steps go per launch, else 0
+    FusedPlan fused;
     ~EstimateState() {
         for (hipEvent_t e : ev)
             if (e) (void)hipEventDestroy(e);
@@ -779,8 +824,8 @@ int sketch_phase(const ld_csr* A, EstimateState& S, hipStream_t st, const VecSto
         // 569 -> 628 us.
         const bool one_plane = (gcol >> 3) == ((gcol + cols - 1) >> 3);
         const int sign_bytes = one_plane && S.planes && S.longrows.dia_nd > 0 ? 1 : 8;
-        if (const int D = keep ? 0 : fused_line(A, S.longrows)) {
-            FusedArgs f = fused_args(A, S.longrows, p, kind, m, cols, D);
+        if (S.fused_D && !keep) {
+            FusedArgs f = fused_args(A, S.longrows, S.fused, kind, m, cols, S.fused_D);
             if (gauss) {
                 void* const sg = S.L.Q1.block(b);
                 LD_CHECK_HIP(launch_gauss_fill(f64, n, cols, S.key0, gcol, 1.0, sg, Blk::plain(S.L.Q1.ld), st));
@@ -792,8 +837,8 @@ int sketch_phase(const ld_csr* A, EstimateState& S, hipStream_t st, const VecSto
                 f.gcol = gcol;
             }
             int launches = 0;
-            LD_CHECK(fused_horner(A, S.longrows, p, f, p.d[0], FusedBlock::rows(Y.block(b), Y.ld, (int)S.L.elem), S.W0,
-                                  S.W1, st, &launches));
+            LD_CHECK(fused_horner(A, S.fused, f, 0.0, FusedBlock::rows(Y.block(b), Y.ld, (int)S.L.elem), S.W0, S.W1, st,
+                                  &launches));
             S.launches1 += launches;
             // each launch reads and writes the block once (the first reads no block)
             S.bytes1 += launches * alg_bytes_step(A, cols, kind, S.L.elem, 5, true, 1) - (double)n * cols * S.L.elem;
@@ -905,23 +950,26 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
     const int nslots = S.mode == LD_DOT_SQUARED ? 2 * ((m + 1) / 2) + 1 : m + 1;
     // partial sums of block b: its own region [slot][workgroup][column of the block]
     const size_t slot_stride = (size_t)L.nwg_dot * X.bw;
+    bool fused = false;
     LD_CHECK(record(S, 2, st));
     for (int b = 0; b < X.nblocks(); ++b) {
         const int cols = X.bcols(b), gcol = b * X.bw;
         double* const part = S.part + (size_t)b * nslots * slot_stride;
         int nwg = 0;
-        const int D = keep || S.mode != LD_DOT_SQUARED ? 0 : fused_line(A, S.longrows);
+        const int D = keep || S.mode != LD_DOT_SQUARED ? 0 : S.fused_D;
         FusedArgs f{};
         FusedGrid grid{};
         if (D) {
-            f = fused_args(A, S.longrows, p, STEP_DOT_SQ, (m + 1) / 2, cols, D);
+            f = fused_args(A, S.longrows, S.fused, STEP_DOT_SQ, (m + 1) / 2, cols, D);
             f.max_parts = L.nwg_dot;
             grid = fused_grid(n, D, cols, (int)L.elem, f.grid_levels, f.max_parts);
         }
-        if (D && grid.parts <= L.nwg_dot) {
+        if (D) {
+            if (grid.parts > L.nwg_dot) return fail(LD_EINVAL, "internal: dot partials overflow");
             const int h = (m + 1) / 2;
             FusedBlock work[2] = {FusedBlock::chunks(S.W0, n, (int)L.elem), FusedBlock::chunks(S.W1, n, (int)L.elem)};
             FusedBlock in = FusedBlock::rows(X.block(b), X.ld, (int)L.elem);
+            fused = true;
             f.slot_stride = (long long)slot_stride;
             f.part_ld = X.bw;
             int w = 0;
@@ -931,7 +979,10 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
                 set_in(f, in);
                 set_out(f, a + f.levels < h ? work[w] : FusedBlock{});   // the last vector feeds no further step
                 f.part = part + (size_t)(a == 0 ? 0 : 2 * a + 1) * slot_stride;
-                for (int t = 0; t < f.levels; ++t) f.beta[t] = p.beta[a + t];
+                for (int t = 0; t < f.levels; ++t) {
+                    f.mid[t] = S.fused.mid[a + t];
+                    f.nbeta[t] = S.fused.nbeta[a + t];
+                }
                 LD_CHECK_HIP(launch_fused(f64, f, st));
                 in = work[w];
                 w = 1 - w;
@@ -999,6 +1050,8 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
                                    L.nc, st));
     }
     LD_CHECK(record(S, 3, st));
+    // the coefficients in the squared basis at the fused launches' centres, while the GPU works
+    if (fused) squared_basis(S.fused.xi, S.fused.d, S.coef);
     S.spmm_launches += S.launches23;
     S.bytes_alg += S.bytes23;
     nu_host.assign((size_t)nslots * L.nc, 0.0);
@@ -1560,7 +1613,18 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
         return fail(LD_EINVAL, "internal: workspace layout overflow");
     if (!o.trusted_csr) LD_CHECK(validate_csr(A, S.flag, st));
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
-    if (!want_grad) LD_CHECK(fit_blocks(A, degree, n_matvec, o, S.longrows, S.L));
+    if (!want_grad) {
+        LD_CHECK(fit_blocks(A, degree, n_matvec, o, S.longrows, S.L));
+        S.fused_D = fused_line(A, S.longrows);
+        if (S.fused_D) {
+            // every block's quadratic forms or none: their coefficients are shared
+            const FusedArgs f = fused_args(A, S.longrows, S.fused, STEP_DOT_SQ, (degree + 1) / 2, S.L.X.bw, S.fused_D);
+            if (fused_grid((int)A->n, S.fused_D, S.L.X.bw, (int)S.L.elem, f.grid_levels, S.L.nwg_dot).parts > S.L.nwg_dot)
+                S.fused_D = 0;
+            else
+                S.fused = fused_plan(A, S.longrows, S.plan);
+        }
+    }
     Timer tm(st, timed);
     tm.mark();
     LD_CHECK(estimate_front(A, seed, S, st, tm, sq_grad ? &B.rs : nullptr));
@@ -1995,6 +2059,19 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     return LD_OK;
 }
 
+// Workspace of ld_apply_log: two blocks as V is stored, or, packed, V and two
+// blocks with rows padded to whole 16-byte vectors (not asked for above
+// kPackMost bytes a block).
+constexpr size_t kPackMost = (size_t)4 << 30;
+
+size_t apply_ws_bytes(const ld_csr* A, int64_t ncols, const ld_options& o, bool packed) {
+    const size_t elem = A->dtype == LD_F64 ? 8 : 4, v = 16 / elem;
+    const size_t rest = align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+    if (!packed) return 2 * align_up((size_t)A->n * (size_t)ncols * elem) + rest;
+    const size_t blk = align_up((size_t)A->n * (((size_t)ncols + v - 1) / v * v) * elem);
+    return blk <= kPackMost ? 3 * blk + rest : 0;
+}
+
 extern "C" {
 
 int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t want_grad,
@@ -2009,9 +2086,7 @@ int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t
         return LD_OK;
     }
     if (n_matvec < 0) {
-        const size_t elem = A->dtype == LD_F64 ? 8 : 4;
-        *bytes = 2 * align_up((size_t)A->n * (size_t)(-(int64_t)n_matvec) * elem) + align_up(256) +
-                 long_rows_bytes(A) + dia_bytes(A, o);
+        *bytes = std::max(apply_ws_bytes(A, -(int64_t)n_matvec, o, false), apply_ws_bytes(A, -(int64_t)n_matvec, o, true));
         return LD_OK;
     }
     if (n_matvec < 3) return fail(LD_EINVAL, "n_matvec must be >= 3");
@@ -2039,36 +2114,81 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
     const uint8_t* v8 = (const uint8_t*)V;
     const uint8_t* p8 = (const uint8_t*)PV;
     if (v8 < p8 + blk && p8 < v8 + blk) return fail(LD_EINVAL, "V and PV overlap");
-    const size_t need = 2 * align_up(blk) + align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+    // a workspace of the size without the packed blocks keeps V's own layout
+    const size_t plain = apply_ws_bytes(A, ncols, o, false), with_pack = apply_ws_bytes(A, ncols, o, true);
+    const bool room = with_pack > 0 && (!workspace || ws_bytes >= with_pack);
     OwnedWs own;
     Arena ar;
-    LD_CHECK(get_workspace(workspace, ws_bytes, need, own, ar));
-    void* B0 = ar.take(blk);
-    void* B1 = ar.take(blk);
+    LD_CHECK(get_workspace(workspace, ws_bytes, room ? std::max(plain, with_pack) : plain, own, ar));
+    const int v = 16 / (int)elem, ldp = padded_ld(nc, (int)elem);
+    const size_t pblk = (size_t)n * ldp * elem;
+    void* const B0 = ar.take(room ? pblk : blk);
+    void* const B1 = ar.take(room ? pblk : blk);
+    void* const B2 = room ? ar.take(pblk) : nullptr;
     int* flag = (int*)ar.take(256);
     if (!o.trusted_csr) LD_CHECK(validate_csr(A, flag, st));
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
     const int m = p.degree;
-    const int cb = (o.block_cols > 0 && o.block_cols < std::min(nc, 64)) ? o.block_cols : std::min(nc, 64);
-    // Horner: r_m = d_m V; r_j = (T - xi_j) r_{j+1} + d_j V, with d_0 carrying
-    // log(sigma); r_m starts in B0, the steps ping-pong B0/B1, step 0 writes PV.
-    LD_CHECK_HIP(launch_scale_copy(f64, n, nc, V, nc, p.d[m], B0, nc, st));
-    const void* cur = B0;
-    for (int j = m - 1; j >= 0; --j) {
-        void* out = j == 0 ? PV : (cur == B0 ? B1 : B0);
-        StepArgs s{};
-        s.kind = STEP_HORNER_VEC;
-        s.win = cur;
-        s.wout = out;
-        s.ld = nc;
-        s.alpha = p.alpha;
-        s.beta = p.beta[j];
-        s.dj = j == 0 ? p.d[0] + std::log(p.sigma) : p.d[j];
-        s.vsrc = V;
-        s.ldv = nc;
-        LD_CHECK(run_step(f64, A, s, nc, cb, st, nullptr, lr));
-        cur = out;
+    const double d0 = p.d[0] + std::log(p.sigma);
+    if (const int D = room && o.block_cols <= 0 ? fused_line(A, lr) : 0) {
+        // column groups whose V and two work blocks fit the Infinity Cache, each
+        // through its whole recurrence; V's chunks are read by every launch
+        const bool whole = nc == v && (uintptr_t)V % 16 == 0 && (uintptr_t)PV % 16 == 0;   // V is one chunk already
+        if (!whole) LD_CHECK_HIP(launch_pack_chunks(f64, n, nc, V, B2, st));
+        const double per_chunk = 3.0 * 16.0 * (double)n;
+        const FusedPlan fp = fused_plan(A, lr, p);
+        const int group = std::max(1, (int)(kBlockPairBudget / per_chunk)) * v;
+        for (int c0 = 0; c0 < nc; c0 += group) {
+            const int cols = std::min(group, nc - c0);
+            const size_t at = (size_t)n * c0 * elem;   // c0 is a whole number of chunks
+            FusedArgs f = fused_args(A, lr, fp, STEP_HORNER_VEC, m, cols, D);
+            const FusedBlock src = FusedBlock::chunks(whole ? const_cast<void*>(V) : (char*)B2 + at, n, (int)elem);
+            f.vsrc = src.p;
+            f.vsrc_cs = src.cs;
+            f.vsrc_rs = src.rs;
+            // the launches write the second, the first, the second ... work block:
+            // ordered so that the last one's is B0
+            const bool odd = (m + f.grid_levels - 1) / f.grid_levels % 2 == 1;
+            void* const W0 = (char*)(odd ? B1 : B0) + at;
+            void* const W1 = (char*)(odd ? B0 : B1) + at;
+            int launches = 0;
+            LD_CHECK(fused_horner(A, fp, f, std::log(p.sigma),
+                                  FusedBlock::chunks(whole ? PV : (char*)B0 + at, n, (int)elem), W0, W1, st, &launches));
+        }
+        if (!whole) LD_CHECK_HIP(launch_unpack_chunks(f64, n, nc, B0, PV, st));
+    } else {
+        // Rows of V that are no whole number of 16-byte vectors (three columns or
+        // more: fewer move less as they are) go through padded copies: the steps'
+        // vector accesses outweigh the two copies from a few steps on.
+        const bool pad = room && o.block_cols <= 0 && nc >= 3 && nc % v != 0 && m >= 4;
+        const int ld = pad ? ldp : nc;
+        const void* src = V;
+        if (pad) {
+            LD_CHECK_HIP(launch_scale_copy(f64, n, nc, V, nc, 1.0, B2, ldp, st));
+            src = B2;
+        }
+        const int cb = (o.block_cols > 0 && o.block_cols < std::min(nc, 64)) ? o.block_cols : std::min(nc, 64);
+        // Horner: r_m = d_m V; r_j = (T - xi_j) r_{j+1} + d_j V, with d_0 carrying
+        // log(sigma); r_m starts in B0, the steps ping-pong B0/B1, step 0 writes PV.
+        LD_CHECK_HIP(launch_scale_copy(f64, n, nc, src, ld, p.d[m], B0, ld, st));
+        const void* cur = B0;
+        for (int j = m - 1; j >= 0; --j) {
+            void* out = j == 0 && !pad ? PV : (cur == B0 ? B1 : B0);
+            StepArgs s{};
+            s.kind = STEP_HORNER_VEC;
+            s.win = cur;
+            s.wout = out;
+            s.ld = ld;
+            s.alpha = p.alpha;
+            s.beta = p.beta[j];
+            s.dj = j == 0 ? d0 : p.d[j];
+            s.vsrc = src;
+            s.ldv = ld;
+            LD_CHECK(run_step(f64, A, s, nc, cb, st, nullptr, lr));
+            cur = out;
+        }
+        if (pad) LD_CHECK_HIP(launch_scale_copy(f64, n, nc, cur, ldp, 1.0, PV, nc, st));
     }
     if (!workspace) LD_CHECK_HIP(hipStreamSynchronize(st));
     return LD_OK;

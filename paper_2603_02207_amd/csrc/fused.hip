@@ -211,15 +211,9 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
             if (k < 2 * t) break;   // level t starts at line y0 - (LV - t) (the same for the whole wave)
             const P &up = ring[t - 1][S2], &mid = ring[t - 1][S1], &dn = ring[t - 1][S];
             P o;
-            // the term that does not come from A: dj S, dj V or nothing
-            auto start = [&](T c, T x, int e) __attribute__((always_inline)) -> T {
-                if constexpr (kSigns) return fma(c, x, with_sign(a.dj[t - 1], meta[t] << (VEC - 1 - e)));
-                if constexpr (kVec) return fma(c, x, a.dj[t - 1] * vline[kVec ? t : 0].v[e]);
-                return c * x;
-            };
             if ((full >> t) & 1u) {
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) o.v[e] = start(a.c[0], up.v[e], e);
+                for (int e = 0; e < VEC; ++e) o.v[e] = a.c[0] * up.v[e];
                 add_shifted<kFromBefore>(o.v, mid.v, a.c[1]);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) o.v[e] = fma(a.mid[t - 1], mid.v[e], o.v[e]);
@@ -232,12 +226,18 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     const T lf = lane_shift<kFromBefore>(mid.v[e]), rt = lane_shift<kFromAfter>(mid.v[e]);
-                    T s = start(a.c[0], (m & 1u) ? up.v[e] : T(0), e);
+                    T s = a.c[0] * ((m & 1u) ? up.v[e] : T(0));
                     s = fma(a.c[1], (m & 2u) ? lf : T(0), s);
                     s = fma(cm, mid.v[e], s);
                     s = fma(a.c[3], (m & 8u) ? rt : T(0), s);
                     o.v[e] = fma(a.c[4], (m & 16u) ? dn.v[e] : T(0), s);
                 }
+            }
+            // last: one rounding at the term's size
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (kSigns) o.v[e] += with_sign(a.dj[t - 1], meta[t] << (VEC - 1 - e));
+                if (kVec) o.v[e] = fma(a.dj[t - 1], vline[kVec ? t : 0].v[e], o.v[e]);
             }
             const int ly = k - t - LV;   // the line's index among the wave's own
             if (kDot && ly >= 0 && ly < ny && own) {
@@ -349,10 +349,10 @@ hipError_t launch_fused_t(const FusedArgs& f, hipStream_t st) {
     d.store = f.wout != nullptr;
     d.nt_out = f.nt_out;
     d.init = (T)f.init_scale;
-    for (int q = 0; q < 5; ++q) d.c[q] = (T)(f.alpha * f.cval[q]);
+    for (int q = 0; q < 5; ++q) d.c[q] = (T)f.off[q];
     for (int t = 0; t < f.levels; ++t) {
-        d.mid[t] = (T)(f.alpha * f.cval[2] - f.beta[t]);
-        d.nbeta[t] = (T)-f.beta[t];
+        d.mid[t] = (T)f.mid[t];
+        d.nbeta[t] = (T)f.nbeta[t];
         d.dj[t] = (T)f.dj[t];
     }
     switch (f.kind) {

@@ -226,6 +226,27 @@ void squared_basis(const std::vector<double>& xi, const std::vector<double>& d,
     for (int i = 0; i <= n; ++i) c[i] = a[i].hi + a[i].lo;
 }
 
+// Moving one centre C_k by eta: the polynomial is nested as a_0 + (x - C_0)[...
+// a_k + (x - C_k) q ...], and (x - C_k) q = (x - C_k') q + eta q, where eta q
+// (Newton coefficients eta a_{k+1..n}, centres C_{k+1..}) is written with C_k'
+// put before its centres by nested multiplication.  The corrections are a
+// factor eta below the coefficients, so FP64 serves.
+void shift_centres(std::vector<double>& centres, const std::vector<double>& to, std::vector<double>& a) {
+    const int n = (int)a.size() - 1;
+    for (int k = n - 1; k >= 0; --k) {
+        const double eta = to[k] - centres[k];
+        centres[k] = to[k];
+        if (eta == 0.0) continue;
+        double r = eta * a[n], old = a[n - 1];   // the correction's last coefficient
+        a[n - 1] += r;
+        for (int t = n - 2; t >= k; --t) {
+            r = eta * old + (centres[k] - centres[t + 1]) * r;
+            old = a[t];
+            a[t] += r;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // SplitMix64 (Steele, Lea & Flood 2014; reference code by S. Vigna).
 // ---------------------------------------------------------------------------

@@ -125,9 +125,10 @@ hipError_t launch_step(bool f64, const CsrDev& A, const StepArgs& s, hipStream_t
 
 // Several Newton steps per launch on a constant five-point stencil (fused.hip; at
 // least kFusedMinWidth rows a line):
-// diagonals at offsets -D, -1, 0, 1, D (cval in that order, bit q of pres[r] =
+// diagonals at offsets -D, -1, 0, 1, D (in that order in off; bit q of pres[r] =
 // row r stores diagonal q).  Level t = 0..levels-1 takes w -> alpha*A*w -
-// beta[t]*w (+ dj[t]*S or + dj[t]*V).  Element (r, c) of a block sits at
+// beta_t*w (+ dj[t]*S or + dj[t]*V), off = alpha times the diagonals' values,
+// mid[t] = off[2] - beta_t.  Element (r, c) of a block sits at
 // (c / VEC)*cs + r*rs + c % VEC, VEC the elements of 16 bytes: row-major rows
 // (cs = VEC, rs = ld) or 16-byte column chunks one after another (cs = n*VEC,
 // rs = VEC).
@@ -173,7 +174,7 @@ struct FusedArgs {
     long long wout_cs;
     int wout_rs;
     const uint16_t* pres;
-    double cval[5];
+    double off[5];                    // alpha * diagonal value
     const uint8_t* planes;
     int gcol;
     const void* vsrc;
@@ -184,8 +185,8 @@ struct FusedArgs {
     int part_ld;
     int max_parts;                    // most partial rows (0: no limit)
     int nt_out;
-    double init_scale, alpha;
-    double beta[kFusedMax], dj[kFusedMax];
+    double init_scale;
+    double mid[kFusedMax], nbeta[kFusedMax], dj[kFusedMax];   // off[2] - beta, -beta
 };
 struct FusedGrid {
     int strips, rows, parts;          // strips of a line, lines of a wave, partial rows
@@ -212,6 +213,12 @@ hipError_t launch_gauss_fill(bool f64, int n, int k, uint64_t key, int col0, dou
 // out[r, c] = scale * V[r, c] (row-major, V with ldv, out with ldo), c < ncols.
 hipError_t launch_scale_copy(bool f64, int n, int ncols, const void* V, int ldv, double scale,
                              void* out, int ldo, hipStream_t st);
+
+// Row-major V (n x ncols, leading dimension ncols, any alignment) to and from
+// 16-byte column chunks one after another (chunk q: n x VEC; columns past ncols
+// are zero).
+hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, void* chunks, hipStream_t st);
+hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, hipStream_t st);
 
 // Partial cross products X^T Z per workgroup, FP64: part[wg][i*kz+j],
 // cross_num_wg(n) rows.  Z is a second block, or, with zmask (one word per

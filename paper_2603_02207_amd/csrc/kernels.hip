@@ -1142,6 +1142,51 @@ hipError_t launch_scale_copy(bool f64, int n, int ncols, const void* V, int ldv,
     return hipGetLastError();
 }
 
+// Row-major <-> column chunks: a wave takes 64 rows of one chunk, a workgroup
+// four chunks of the same rows (their pieces of a row share cache lines).
+template <typename T, bool PACK>
+__global__ __launch_bounds__(kThreads) void chunk_copy_kernel(int n, int ncols, T* __restrict__ V, T* __restrict__ chunks) {
+    constexpr int V16 = 16 / (int)sizeof(T);
+    const int r = blockIdx.x * 64 + (threadIdx.x & 63), q = blockIdx.y * kWaves + (threadIdx.x >> 6);
+    if (r >= n || q * V16 >= ncols) return;
+    T* const row = V + (size_t)r * ncols + q * V16;
+    T* const at = chunks + ((size_t)q * n + r) * V16;
+    const int have = min(V16, ncols - q * V16);
+    Pack<T, V16> p;
+    if constexpr (PACK) {
+#pragma unroll
+        for (int e = 0; e < V16; ++e) p.v[e] = e < have ? row[e] : T(0);
+        store_pack<T, V16>(at, p);
+    } else {
+        p = load_pack<T, V16>(at);
+#pragma unroll
+        for (int e = 0; e < V16; ++e)
+            if (e < have) row[e] = p.v[e];
+    }
+}
+
+template <bool PACK>
+hipError_t launch_chunk_copy(bool f64, int n, int ncols, void* V, void* chunks, hipStream_t st) {
+    if (n == 0 || ncols == 0) return hipSuccess;
+    const int nq = div_up(ncols, f64 ? 2 : 4);
+    const dim3 grid(div_up(n, 64), div_up(nq, kWaves));
+    if (grid.y > 65535) return hipErrorInvalidValue;
+    if (f64)
+        hipLaunchKernelGGL((chunk_copy_kernel<double, PACK>), grid, dim3(kThreads), 0, st, n, ncols, (double*)V,
+                           (double*)chunks);
+    else
+        hipLaunchKernelGGL((chunk_copy_kernel<float, PACK>), grid, dim3(kThreads), 0, st, n, ncols, (float*)V,
+                           (float*)chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, void* chunks, hipStream_t st) {
+    return launch_chunk_copy<true>(f64, n, ncols, const_cast<void*>(V), chunks, st);
+}
+hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, hipStream_t st) {
+    return launch_chunk_copy<false>(f64, n, ncols, V, const_cast<void*>(chunks), st);
+}
+
 // ---------------------------------------------------------------------------
 // X^T Z on FP64 MFMA (v_mfma_f64_16x16x4_f64).  Operand layout of the 16x16x4
 // instruction: lane l holds A[l%16][l/16] and B[l/16][l%16]; the 16x16 result

@@ -27,6 +27,10 @@ int divided_differences(double lo, double hi, int degree, int s_mode, int64_t ca
 void squared_basis(const std::vector<double>& xi, const std::vector<double>& d,
                    std::vector<double>& c);
 
+// The Newton coefficients a (a.size() - 1 centres) of a polynomial, moved to the
+// centres `to`, each close to the old one (centres becomes `to`).
+void shift_centres(std::vector<double>& centres, const std::vector<double>& to, std::vector<double>& a);
+
 // SplitMix64 pieces (published generator, Steele-Lea-Flood 2014).
 uint64_t splitmix_mix(uint64_t z);
 uint64_t probe_stream_key(uint64_t seed, int stream);

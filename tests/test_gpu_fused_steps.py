@@ -10,8 +10,8 @@ import numpy as np
 import pytest
 
 import workloads as w
-from oracle import bounds, hutchpp
-from tests.gpu_common import assert_cols_close  # noqa: F401
+from oracle import bounds, hutchpp, newton
+from tests.gpu_common import assert_cols_close, random_spd_csr
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +73,48 @@ def test_fused_steps_against_oracle(width, lines, cut, holes, wrap, degree, quer
     ref_g = hutchpp.logdet_estimate(w.to_scipy((csr[0], csr[1], vals, csr[3])), lo, hi, degree, queries, 3,
                                     probes="gaussian")
     assert abs(ld.logdet(A, lo, hi, degree, queries, 3, options=gauss) - ref_g) < tol * abs(ref_g)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("kind", ["fused", "stencil", "csr"])
+def test_apply_log_column_counts(kind, dtype):
+    """log(A) V at column counts around whole 16-byte vectors: launches of several steps on packed chunks (one
+    chunk used in place, a misaligned V, several chunks), and padded copies of V elsewhere; a workspace too
+    small for the packed blocks gives the same columns.  1e-12 / 2e-5 of a column's largest entry."""
+    csr = {"fused": lambda: stencil(150, 31, 7, 3), "stencil": lambda: stencil(30, 40),
+           "csr": lambda: random_spd_csr(1500, 3, density=0.01, long_rows=1)}[kind]()
+    n = csr[3]
+    A = ld.CSR.from_arrays(csr[0], csr[1], np.asarray(csr[2]), n, dtype=dtype)
+    vals = A.val.double().cpu().numpy()
+    lo, hi = (0.25, 8.4) if kind != "csr" else bounds.gershgorin((csr[0], csr[1], vals, n))
+    Q = w.to_scipy((csr[0], csr[1], vals, n))
+    rng = np.random.default_rng(1)
+    tol = 1e-12 if dtype == torch.float64 else 2e-5
+    for cols, degree in ((1, 9), (2, 4), (3, 5), (4, 8), (5, 3), (17, 12), (67, 4)):
+        store = torch.tensor(rng.standard_normal(n * cols + 1), dtype=dtype, device="cuda")
+        for shift in (0, 1):   # V at an odd element: rows on no vector boundary
+            V = store[shift:shift + n * cols].view(n, cols)
+            out = ld.apply_log(A, lo, hi, degree, V).double().cpu().numpy()
+            ref = newton.apply_log(Q, V.double().cpu().numpy(), lo, hi, degree)
+            assert_cols_close(out, ref, tol)
+    # the size without packed blocks is still accepted
+    import ctypes
+
+    from paper_2603_02207_amd import _native as nat
+    c, o = A.c_struct(), ld.Options().to_c()
+    b = ctypes.c_size_t(0)
+    nat.check(nat.load().ld_workspace_size(ctypes.byref(c), 12, -17, 0, ctypes.byref(o), ctypes.byref(b)), "size")
+    elem = 8 if dtype == torch.float64 else 4
+    pad = -(-(n * 20 if elem == 4 else n * 18) * elem // 256) * 256
+    plain = b.value - 3 * pad + 2 * (-(-n * 17 * elem // 256) * 256)
+    V = torch.tensor(rng.standard_normal((n, 17)), dtype=dtype, device="cuda")
+    small, out = torch.empty(plain, dtype=torch.uint8, device="cuda"), torch.empty_like(V)
+    args = (ctypes.byref(c), float(lo), float(hi), 12, ctypes.c_void_p(V.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+            17, ctypes.byref(o), ctypes.c_void_p(small.data_ptr()))
+    assert nat.load().ld_apply_log(*args, plain, None) == nat.LD_OK
+    torch.cuda.synchronize()
+    assert_cols_close(out.double().cpu().numpy(), newton.apply_log(Q, V.double().cpu().numpy(), lo, hi, 12), tol)
+    assert nat.load().ld_apply_log(*args, plain - 256, None) == nat.LD_EWORKSPACE
 
 
 def test_bounds_of_the_cases():
