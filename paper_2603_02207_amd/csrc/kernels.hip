@@ -426,6 +426,177 @@ __global__ __launch_bounds__(NT) void step_kernel(
     }
 }
 
+// The Newton update of one row's VEC columns from its products acc = (A w)[row],
+// and the row's part of the column sums.
+template <typename T>
+struct RowUpdate {
+    const T* win;
+    T* wout;
+    int ld, c0, gshift;
+    T alpha, beta, dj;
+    const T* vsrc;
+    int ldv;
+    const uint64_t* mask;
+    T* accum;
+    int ldacc, acc_cols;
+    const uint64_t* active;
+    int nt_out;
+};
+
+template <typename T, int VEC, int KIND, bool FIRST>
+__device__ __forceinline__ void row_update(const RowUpdate<T>& u, int row, int col, const T (&acc)[VEC],
+                                           double (&s0)[VEC], double (&s1)[VEC], double (&s2)[VEC]) {
+    const Pack<T, VEC> w = load_pack<T, VEC>(u.win + (size_t)row * u.ld + col);
+    Pack<T, VEC> o;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) o.v[e] = u.alpha * acc[e] - u.beta * w.v[e];
+    if constexpr (KIND == STEP_HORNER_SIGNS) {
+        const uint64_t bits = u.mask[row];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const T sgn = ((bits >> ((col + u.gshift + e) & 63)) & 1ull) ? T(-1) : T(1);
+            o.v[e] = fma(u.dj, sgn, o.v[e]);
+        }
+    } else if constexpr (KIND == STEP_HORNER_VEC) {
+        const Pack<T, VEC> v = load_pack<T, VEC>(u.vsrc + (size_t)row * u.ldv + col);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o.v[e] = fma(u.dj, v.v[e], o.v[e]);
+    } else if constexpr (KIND == STEP_DOT_FWD) {
+        const Pack<T, VEC> x = load_pack<T, VEC>(u.vsrc + (size_t)row * u.ldv + col);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            if (FIRST) s0[e] += (double)x.v[e] * (double)w.v[e];
+            s1[e] += (double)x.v[e] * (double)o.v[e];
+        }
+    } else if constexpr (KIND == STEP_DOT_SQ) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            if (FIRST) s0[e] += (double)w.v[e] * (double)w.v[e];
+            s1[e] += (double)w.v[e] * (double)o.v[e];
+            s2[e] += (double)o.v[e] * (double)o.v[e];
+        }
+    } else if constexpr (KIND == STEP_ACC_NORM) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s1[e] += (double)o.v[e] * (double)o.v[e];
+    }
+    if constexpr (KIND == STEP_PLAIN_ACC || KIND == STEP_ACC_NORM) {
+        if (col < u.acc_cols) {
+            const uint64_t bits = KIND == STEP_ACC_NORM ? *u.active : ~0ull;
+            T* const pa = u.accum + (size_t)row * u.ldacc + col;
+            const Pack<T, VEC> a0 = load_pack<T, VEC>(pa);
+            Pack<T, VEC> a1;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const int b = col - u.c0 + e;
+                const bool on = KIND == STEP_PLAIN_ACC || (b < 64 && ((bits >> (b & 63)) & 1ull));
+                a1.v[e] = on ? fma(u.dj, o.v[e], a0.v[e]) : a0.v[e];
+            }
+            store_pack<T, VEC>(pa, a1);
+        }
+    }
+    if (u.nt_out)
+        store_pack_nt<T, VEC>(u.wout + (size_t)row * u.ld + col, o);
+    else
+        store_pack<T, VEC>(u.wout + (size_t)row * u.ld + col, o);
+}
+
+// ---------------------------------------------------------------------------
+// Newton step on CSR rows of more than a few entries: a row's entries are dealt
+// round-robin to `slices` groups of lpr lanes (slice s takes entries s, s +
+// slices, ...; lane li of a slice owns VEC columns), kSliceBatch entries of a
+// slice in flight together, and the slices' sums meet in a shuffle tree.  Next
+// to the row groups of step_kernel (one group walks a whole row, a batch of
+// entries after another) a row takes a few dependent loads whatever its length,
+// and a small matrix gives the device more waves.  Column sums: as in
+// long_row_kernel, one partial row per workgroup, waves in order.  Measured on
+// gfx950, mesh of 36441 rows and 15.5 entries each, FP64: sketch step over 4
+// columns 12.2 -> 5.8 us, quadratic forms over 8 columns 15.1 -> 9.4 us.
+// ---------------------------------------------------------------------------
+constexpr int kSliceBatch = 4;
+
+template <typename T, int VEC, int KIND, bool FIRST>
+__global__ __launch_bounds__(kThreads) void csr_slice_kernel(
+    int n, const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const T* __restrict__ val,
+    const RowUpdate<T> up, int bcols, double* __restrict__ ps0, double* __restrict__ ps1, double* __restrict__ ps2,
+    int part_ld, int lpr, int slices, int skip_long, int ntiles, int interleave) {
+    constexpr bool kDot = is_dot(KIND);
+    constexpr int U = kSliceBatch;
+    __shared__ double s_sum[kDot ? kWaves * 64 * VEC : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int span = lpr * slices, rpw = 64 / span;   // lanes of a row, rows of a wave
+    const int g = lane / span, at = lane - g * span, sl = at / lpr, li = at - sl * lpr;
+    const bool lane_ok = g < rpw;
+    const int col = up.c0 + li * VEC;
+    double s0[VEC], s1[VEC], s2[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) s0[e] = s1[e] = s2[e] = 0.0;
+    // tiles of kWaves * rpw rows: XCD bands or interleaved, as step_kernel
+    const int xcd = blockIdx.x % kXcds, base = ntiles / kXcds, rem = ntiles % kXcds;
+    const int band0 = interleave ? 0 : xcd * base + (xcd < rem ? xcd : rem);
+    const int band_len = interleave ? ntiles : base + (xcd < rem ? 1 : 0);
+    const int stride =
+        interleave ? (int)gridDim.x : (int)(gridDim.x / kXcds) + (xcd < (int)(gridDim.x % kXcds) ? 1 : 0);
+    for (int t = interleave ? (int)blockIdx.x : (int)(blockIdx.x / kXcds); t < band_len; t += stride) {
+        const int row = (band0 + t) * (kWaves * rpw) + wave * rpw + g;
+        int beg = 0, end = 0;
+        if (lane_ok && row < n) {
+            beg = row_ptr[row];
+            end = row_ptr[row + 1];
+        }
+        const bool mine = lane_ok && row < n && !(skip_long && end - beg > kLongRow);   // else long_row_kernel's
+        if (!mine) end = beg;
+        T acc[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] = T(0);
+        for (int k = beg + sl; k < end; k += U * slices) {
+            int cc[U];
+            T aa[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool on = k + u * slices < end;
+                cc[u] = on ? (up.nt_out ? __builtin_nontemporal_load(col_idx + k + u * slices) : col_idx[k + u * slices]) : -1;
+                aa[u] = on ? (up.nt_out ? __builtin_nontemporal_load(val + k + u * slices) : val[k + u * slices]) : T(0);
+            }
+            Pack<T, VEC> x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (cc[u] >= 0) x[u] = load_pack<T, VEC>(up.win + (size_t)cc[u] * up.ld + col);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (cc[u] >= 0)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc[e] = fma(aa[u], x[u].v[e], acc[e]);
+        }
+        for (int h = slices / 2; h >= 1; h >>= 1) {   // slices is a power of two
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const T o = __shfl(acc[e], lane + h * lpr, 64);
+                if (sl < h) acc[e] += o;
+            }
+        }
+        if (mine && sl == 0) row_update<T, VEC, KIND, FIRST>(up, row, col, acc, s0, s1, s2);
+    }
+    if constexpr (kDot) {
+        const size_t prow = (size_t)blockIdx.x * part_ld + up.c0 + up.gshift;
+        auto total = [&](const double(&v)[VEC], double* dst) __attribute__((always_inline)) {
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) s_sum[threadIdx.x * VEC + e] = v[e];
+            __syncthreads();
+            for (int t = threadIdx.x; t < bcols; t += kThreads) {
+                const int tl = t / VEC, te = t - tl * VEC;
+                double a = 0.0;
+                for (int wv = 0; wv < kWaves; ++wv)
+                    for (int gg = 0; gg < rpw; ++gg) a += s_sum[(wv * 64 + gg * span + tl) * VEC + te];
+                dst[prow + t] = a;
+            }
+        };
+        if (FIRST) total(s0, ps0);
+        total(s1, ps1);
+        if (KIND == STEP_DOT_SQ) total(s2, ps2);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Long rows: a wave per row, or the whole workgroup for rows above kCoopRow
 // entries.  The row's entries are dealt round-robin to the row groups at work
@@ -516,57 +687,9 @@ __global__ __launch_bounds__(256) void long_row_kernel(
             }
         }
     };
-    // the Newton update of the row, by the lanes of one row group
+    const RowUpdate<T> up{win, wout, ld, c0, gshift, alpha, beta, dj, vsrc, ldv, mask, accum, ldacc, acc_cols, active, 0};
     auto finish = [&](int row, const T(&acc)[VEC]) __attribute__((always_inline)) {
-        const Pack<T, VEC> w = load_pack<T, VEC>(win + (size_t)row * ld + col);
-        Pack<T, VEC> o;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) o.v[e] = alpha * acc[e] - beta * w.v[e];
-        if constexpr (KIND == STEP_HORNER_SIGNS) {
-            const uint64_t bits = mask[row];
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const T sgn = ((bits >> ((col + gshift + e) & 63)) & 1ull) ? T(-1) : T(1);
-                o.v[e] = fma(dj, sgn, o.v[e]);
-            }
-        } else if constexpr (KIND == STEP_HORNER_VEC) {
-            const Pack<T, VEC> v = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) o.v[e] = fma(dj, v.v[e], o.v[e]);
-        } else if constexpr (KIND == STEP_DOT_FWD) {
-            const Pack<T, VEC> x = load_pack<T, VEC>(vsrc + (size_t)row * ldv + col);
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                if (FIRST) s0[e] += (double)x.v[e] * (double)w.v[e];
-                s1[e] += (double)x.v[e] * (double)o.v[e];
-            }
-        } else if constexpr (KIND == STEP_DOT_SQ) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                if (FIRST) s0[e] += (double)w.v[e] * (double)w.v[e];
-                s1[e] += (double)w.v[e] * (double)o.v[e];
-                s2[e] += (double)o.v[e] * (double)o.v[e];
-            }
-        } else if constexpr (KIND == STEP_ACC_NORM) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) s1[e] += (double)o.v[e] * (double)o.v[e];
-        }
-        if constexpr (KIND == STEP_PLAIN_ACC || KIND == STEP_ACC_NORM) {
-            if (col < acc_cols) {
-                const uint64_t bits = KIND == STEP_ACC_NORM ? *active : ~0ull;
-                T* const pa = accum + (size_t)row * ldacc + col;
-                const Pack<T, VEC> a0 = load_pack<T, VEC>(pa);
-                Pack<T, VEC> a1;
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const int b = col - c0 + e;
-                    const bool on = KIND == STEP_PLAIN_ACC || (b < 64 && ((bits >> (b & 63)) & 1ull));
-                    a1.v[e] = on ? fma(dj, o.v[e], a0.v[e]) : a0.v[e];
-                }
-                store_pack<T, VEC>(pa, a1);
-            }
-        }
-        store_pack<T, VEC>(wout + (size_t)row * ld + col, o);
+        row_update<T, VEC, KIND, FIRST>(up, row, col, acc, s0, s1, s2);
     };
 
     T acc[VEC];
@@ -871,6 +994,46 @@ hipError_t launch_step_t(const CsrDev& A, const StepArgs& s, hipStream_t st, int
     }
     if (s.ranges_out) *s.ranges_out = 1;
     const int skip = s.long_rows != nullptr;
+    auto long_rows = [&](int part_row0) {
+        hipLaunchKernelGGL((long_row_kernel<T, VEC, KIND, FIRST>), dim3(kLongWgs), dim3(256), 0, st,
+                           A.n, A.row_ptr, A.col_idx, (const T*)A.val, (const T*)s.win, (T*)s.wout, s.ld,
+                           s.c0, s.bcols, s.gshift, (T)s.alpha, (T)s.beta, (T)s.dj, (const T*)s.vsrc,
+                           s.ldv, s.mask, s.ps0, s.ps1, s.ps2, s.part_ld, lpr, rpw, s.long_rows,
+                           s.long_count, part_row0, (T*)s.acc, s.ldacc, s.acc_cols, s.active);
+        return hipGetLastError();
+    };
+    // Rows of more than kMaxDiag entries on average go in slices; at most that
+    // many (every matrix that the diagonal storage could hold among them) keep a
+    // row group per row, whose sums are the diagonal storage's in its order.
+    // Slices pay while the row groups' own tiles are too few to fill the device,
+    // and for the kinds with column sums, whose workgroups walk several tiles one
+    // after another, only where a slice is narrow or the rows' lengths differ
+    // much.  Measured (us per step; 1, 2, 4, 8 slices), mesh of 15.5 entries a
+    // row: sketch, 36441 rows, 4 FP64 columns 12.2, 6.2, 5.8, 6.6, 20 FP32
+    // columns 12.5, 8.9, 8.8, 15.2; 400000 rows (3125 tiles), 8 FP64 columns
+    // 57.7, 46.7, 56.1, (4166 tiles) 20 FP32 columns 50.3, 59.3, 67.3; quadratic
+    // forms, 36441 rows, 8 FP64 columns 15.1, 9.4, 10.1, 11.0, 20 columns 11.7,
+    // 15.6, 19.5; power-law graph of 300000 rows, 20 FP32 columns 136, 122, 119.
+    int slices = ntiles < 2048 ? 4 : ntiles < 4096 ? 2 : 1;
+    if (is_dot(KIND)) slices = (ntiles < 2048 && lpr <= 4) || (ntiles < 4096 && s.interleave) ? 2 : 1;
+    while (slices > 1 && lpr * slices > 32) slices /= 2;
+    if ((long long)A.nnz > (long long)kMaxDiag * A.n && slices > 1) {
+        const int rows = kWaves * (64 / (lpr * slices)), tiles = div_up(A.n, rows);
+        // (the partial rows of the long-row launch too, where there is none)
+        const int most = step_num_wg_bound(A.n, s.bcols, (int)sizeof(T)) - (skip ? kLongWgs : 0);
+        const int nwg = is_dot(KIND) ? std::min({tiles, most,
+                                                 resident_wgs(reinterpret_cast<const void*>(csr_slice_kernel<T, VEC, KIND, has_first(KIND)>), kThreads),
+                                                 resident_wgs(reinterpret_cast<const void*>(csr_slice_kernel<T, VEC, KIND, false>), kThreads)})
+                                     : tiles;
+        if (nwg_out) *nwg_out = nwg + (skip ? kLongWgs : 0);
+        const RowUpdate<T> up{(const T*)s.win, (T*)s.wout, s.ld, s.c0, s.gshift, (T)s.alpha, (T)s.beta, (T)s.dj,
+                              (const T*)s.vsrc, s.ldv, s.mask, (T*)s.acc, s.ldacc, s.acc_cols, s.active, s.nt_out};
+        hipLaunchKernelGGL((csr_slice_kernel<T, VEC, KIND, FIRST>), dim3(nwg), dim3(kThreads), 0, st, A.n, A.row_ptr,
+                           A.col_idx, (const T*)A.val, up, s.bcols, s.ps0, s.ps1, s.ps2, s.part_ld, lpr, slices, skip,
+                           tiles, s.interleave || nwg < std::min(tiles, kXcds));   // bands need a workgroup on every XCD
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess || !skip ? e : long_rows(nwg);
+    }
     const auto fn = step_kernel<T, VEC, KIND, FIRST, kIters, NT, 0>;
     const int nwg = grid(reinterpret_cast<const void*>(step_kernel<T, VEC, KIND, has_first(KIND), kIters, NT, 0>),
                          reinterpret_cast<const void*>(step_kernel<T, VEC, KIND, false, kIters, NT, 0>));
@@ -881,14 +1044,8 @@ hipError_t launch_step_t(const CsrDev& A, const StepArgs& s, hipStream_t st, int
                        s.ldv, s.mask, s.ps0, s.ps1, s.ps2, s.part_ld, lpr, rpw, skip, (T*)s.acc,
                        s.ldacc, s.acc_cols, ntiles, s.active, (const T*)nullptr, 0, off, s.interleave, ctiles,
                        s.nt_out, (const uint16_t*)nullptr, cv, 0, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !skip) return e;
-    hipLaunchKernelGGL((long_row_kernel<T, VEC, KIND, FIRST>), dim3(kLongWgs), dim3(256), 0, st,
-                       A.n, A.row_ptr, A.col_idx, (const T*)A.val, (const T*)s.win, (T*)s.wout, s.ld,
-                       s.c0, s.bcols, s.gshift, (T)s.alpha, (T)s.beta, (T)s.dj, (const T*)s.vsrc,
-                       s.ldv, s.mask, s.ps0, s.ps1, s.ps2, s.part_ld, lpr, rpw, s.long_rows,
-                       s.long_count, nwg, (T*)s.acc, s.ldacc, s.acc_cols, s.active);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || !skip ? e : long_rows(nwg);
 }
 
 template <typename T, int VEC>
