@@ -118,9 +118,10 @@ typedef struct {
                                 in the same order at the same column blocks,
                                 but the default blocks follow the stored bytes
                                 (see block_cols), the gradient groups its
-                                per-entry sums differently, and a constant
-                                five-point stencil with lines of 128 rows or
-                                more takes several Newton steps per launch
+                                per-entry sums differently, a constant five-
+                                point stencil with lines of 128 rows or more
+                                takes several Newton steps per launch, and a
+                                matrix whose arrays fit a CU's LDS all of them
                                 (see tile_order): equal to rounding there)    */
     int32_t tile_order;      /* LD_TILES_AUTO / LD_TILES_XCD_BANDS /
                                 LD_TILES_INTERLEAVED: how the workgroups of a

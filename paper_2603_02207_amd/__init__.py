@@ -158,7 +158,7 @@ def logdet(A: CSR, lmin: float, lmax: float, degree: int, n_matvec: int, seed: i
                                      int(n_matvec), ctypes.c_uint64(int(seed) & (2**64 - 1)),
                                      ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
                                      _stream_handle(A.val.device), ctypes.byref(out),
-                                     ctypes.byref(st)), "ld_logdet_estimate")
+                                     ctypes.byref(st) if return_stats else None), "ld_logdet_estimate")
     if return_stats:
         return out.value, st.as_dict()
     return out.value
@@ -183,7 +183,7 @@ def logdet_adaptive(A: CSR, lmin: float, lmax: float, max_degree: int, tol: floa
         ctypes.byref(c), float(lmin), float(lmax), int(max_degree), float(tol), int(n_matvec),
         ctypes.c_uint64(int(seed) & (2**64 - 1)), ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
         _stream_handle(A.val.device), ctypes.byref(out), degrees.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
-        ctypes.byref(st)), "ld_logdet_estimate_adaptive")
+        ctypes.byref(st) if return_stats else None), "ld_logdet_estimate_adaptive")
     if return_stats:
         return out.value, degrees, st.as_dict()
     return out.value, degrees
@@ -203,7 +203,7 @@ def logdet_noalloc(A: CSR, lmin: float, lmax: float, degree: int, n_matvec: int,
         nat.check(lib.ld_logdet_estimate_noalloc(ctypes.byref(c), float(lmin), float(lmax), int(degree),
                                                  int(n_matvec), ctypes.c_uint64(int(seed) & (2**64 - 1)),
                                                  ctypes.byref(o), _stream_handle(A.val.device),
-                                                 ctypes.byref(out), ctypes.byref(st)),
+                                                 ctypes.byref(out), ctypes.byref(st) if return_stats else None),
                   "ld_logdet_estimate_noalloc")
     if return_stats:
         return out.value, st.as_dict()
@@ -226,7 +226,8 @@ def logdet_with_grad(A: CSR, lmin: float, lmax: float, degree: int, n_matvec: in
                                  int(n_matvec), ctypes.c_uint64(int(seed) & (2**64 - 1)),
                                  ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
                                  _stream_handle(A.val.device), ctypes.byref(out),
-                                 ctypes.c_void_p(grad.data_ptr()), ctypes.byref(st)), "ld_logdet_grad")
+                                 ctypes.c_void_p(grad.data_ptr()),
+                                 ctypes.byref(st) if return_stats else None), "ld_logdet_grad")
     if return_stats:
         return out.value, grad, st.as_dict()
     return out.value, grad

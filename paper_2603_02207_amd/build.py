@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libleja_logdet.so")
-SOURCES = ["host_math.cpp", "kernels.hip", "fused.hip", "lanczos.hip", "api.hip"]
+SOURCES = ["host_math.cpp", "kernels.hip", "fused.hip", "lanczos.hip", "resident.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "-O3",

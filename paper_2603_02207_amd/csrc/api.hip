@@ -118,15 +118,6 @@ int csr_status(const int* h) {
     return LD_OK;
 }
 
-int validate_csr(const ld_csr* A, int* dflag, hipStream_t st) {
-    LD_CHECK_HIP(hipMemsetAsync(dflag, 0, 2 * sizeof(int), st));
-    LD_CHECK_HIP(launch_validate_csr(dev_of(A), dflag, st));
-    int h[2] = {0, 0};
-    LD_CHECK_HIP(hipMemcpyAsync(h, dflag, sizeof(h), hipMemcpyDeviceToHost, st));
-    LD_CHECK_HIP(hipStreamSynchronize(st));
-    return csr_status(h);
-}
-
 // ---------------------------------------------------------------------------
 // Column blocking.  Each n x b block of probe columns runs its own recurrence
 // (columns never interact inside it), so a matrix of many columns can be
@@ -628,7 +619,19 @@ int fused_horner(const ld_csr* A, const FusedPlan& q, FusedArgs f, double add, c
     return LD_OK;
 }
 
-// Per-call matrix preparation, with one host sync for all results: the list
+// Matrices whose recurrences run in one launch (resident.hip): the CSR arrays
+// and a column chunk fit a CU's LDS, and no row is so long that the thread
+// walking it holds up the others.  An explicit tile order or column block keeps
+// one launch per step.
+bool resident_fits(const ld_csr* A, const LongRows& lr, const ld_options& o, int steps) {
+    return lr.tile_order == LD_TILES_AUTO && o.block_cols <= 0 && !lr.list && A->nnz > 0 && steps <= kResidentSteps &&
+           A->n <= 8 * 1024 &&
+           resident_lds(A->n, A->nnz, A->dtype == LD_F64 ? 8 : 4) <= (size_t)kResidentLds;
+}
+
+// Per-call matrix preparation, with one host sync for all results: the check of
+// the CSR structure (unless the caller vouches for it; nothing here reads out
+// of range whatever the arrays hold), the list
 // of rows with more than kLongRow entries, the balance of the entries over
 // the eight row bands (tile order), and diagonal storage when every stored
 // entry lies on one of at most kMaxDiag diagonals (stencils, banded
@@ -640,23 +643,23 @@ int prepare_rows(const ld_csr* A, const ld_options& o, Arena& ar, hipStream_t st
         return fail(LD_EINVAL, "tile_order must be LD_TILES_AUTO, LD_TILES_XCD_BANDS or LD_TILES_INTERLEAVED");
     int* list = (int*)ar.take((size_t)A->n * 4);
     int* tmp = (int*)ar.take(((size_t)A->n / 256 + 4) * 4);
-    int* count = (int*)ar.take(16);
+    (void)ar.take(16);
     void* buf = o.csr_only ? nullptr : ar.take((size_t)A->n * kMaxDiag * (A->dtype == LD_F64 ? 8 : 4));
     uint16_t* pres = o.csr_only ? nullptr : (uint16_t*)ar.take((size_t)A->n * 2);
     int* info = (int*)ar.take(256);
     const bool probe = A->n >= 3 && A->nnz > 0;
     const bool want_dia = buf && probe;
-    int hcount = 0;
     int h[64] = {};   // the 256-byte info block
-    LD_CHECK_HIP(launch_long_rows(dev_of(A), tmp, list, count, st));
+    LD_CHECK_HIP(hipMemsetAsync(info, 0, sizeof(h), st));
+    if (!o.trusted_csr) LD_CHECK_HIP(launch_validate_csr(dev_of(A), info + kCheckInfo, st));
+    LD_CHECK_HIP(launch_long_rows(dev_of(A), tmp, list, info + kLongInfo, st));
     if (probe) {
-        LD_CHECK_HIP(hipMemcpyAsync(info, h, sizeof(h), hipMemcpyHostToDevice, st));
         LD_CHECK_HIP(launch_rows_probe(A->dtype == LD_F64, dev_of(A), info, st));
         if (want_dia) LD_CHECK_HIP(launch_dia_build(A->dtype == LD_F64, dev_of(A), buf, pres, info, st));
-        LD_CHECK_HIP(hipMemcpyAsync(h, info, sizeof(h), hipMemcpyDeviceToHost, st));
     }
-    LD_CHECK_HIP(hipMemcpyAsync(&hcount, count, sizeof(int), hipMemcpyDeviceToHost, st));
-    LD_CHECK_HIP(hipStreamSynchronize(st));   // also orders the upload of h before its reuse
+    LD_CHECK_HIP(hipMemcpyAsync(h, info, sizeof(h), hipMemcpyDeviceToHost, st));
+    LD_CHECK_HIP(hipStreamSynchronize(st));
+    LD_CHECK(csr_status(h + kCheckInfo));
     lr = LongRows{};
     lr.tile_order = o.tile_order;
     if (probe) {   // skewed: some band holds more than 1.25x its share of the entries
@@ -665,9 +668,9 @@ int prepare_rows(const ld_csr* A, const ld_options& o, Arena& ar, hipStream_t st
         lr.skewed = (double)most * kXcds > 1.25 * (double)A->nnz;
         lr.scattered = 2 * h[kFarInfo] > h[kFarInfo + 1];
     }
-    if (hcount > 0) {
+    if (h[kLongInfo] > 0) {
         lr.list = list;
-        lr.count = count;
+        lr.count = info + kLongInfo;
     }
     const int nd = h[0];
     if (want_dia && nd >= 1 && nd <= kMaxDiag && !h[12]) {
@@ -723,6 +726,7 @@ struct EstimateState {
     bool timed = true;              // false: no HIP events (ld_logdet_estimate_noalloc)
     LongRows longrows;
     int fused_D = 0;                // line length where several steps go per launch, else 0
+    bool resident = false;          // whole recurrences in one launch
     FusedPlan fused;
     ~EstimateState() {
         for (hipEvent_t e : ev)
@@ -824,6 +828,30 @@ int sketch_phase(const ld_csr* A, EstimateState& S, hipStream_t st, const VecSto
         // 569 -> 628 us.
         const bool one_plane = (gcol >> 3) == ((gcol + cols - 1) >> 3);
         const int sign_bytes = one_plane && S.planes && S.longrows.dia_nd > 0 ? 1 : 8;
+        if (S.resident && !keep) {
+            ResidentArgs f{};
+            f.kind = kind;
+            f.cols = cols;
+            f.steps = m;
+            if (gauss) {
+                f.src = S.L.Q1.block(b);
+                f.src_ld = S.L.Q1.ld;
+                LD_CHECK_HIP(launch_gauss_fill(f64, n, cols, S.key0, gcol, 1.0, S.L.Q1.block(b), Blk::plain(S.L.Q1.ld), st));
+            }
+            f.out = Y.block(b);
+            f.out_ld = Y.ld;
+            f.mask = (const uint64_t*)S.mask;
+            f.gcol = gcol;
+            f.alpha = p.alpha;
+            f.init = p.d[m];
+            const std::vector<double> beta(p.beta.rbegin(), p.beta.rend()), d(p.d.rbegin() + 1, p.d.rend());
+            f.beta = beta.data();
+            f.d = d.data();
+            LD_CHECK_HIP(launch_resident(f64, dev_of(A), f, st));
+            S.launches1 += 1;
+            S.bytes1 += (double)n * cols * S.L.elem + matrix_bytes(A, S.L.elem) + 8.0 * n;
+            continue;
+        }
         if (S.fused_D && !keep) {
             FusedArgs f = fused_args(A, S.longrows, S.fused, kind, m, cols, S.fused_D);
             if (gauss) {
@@ -964,7 +992,23 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
             f.max_parts = L.nwg_dot;
             grid = fused_grid(n, D, cols, (int)L.elem, f.grid_levels, f.max_parts);
         }
-        if (D) {
+        if (S.resident && !keep && S.mode == LD_DOT_SQUARED) {
+            ResidentArgs f{};
+            f.kind = STEP_DOT_SQ;
+            f.cols = cols;
+            f.steps = (m + 1) / 2;
+            f.src = X.block(b);
+            f.src_ld = X.ld;
+            f.part = part;
+            f.slot_stride = (long long)slot_stride;
+            f.part_ld = X.bw;
+            f.alpha = p.alpha;
+            f.beta = p.beta.data();
+            LD_CHECK_HIP(launch_resident(f64, dev_of(A), f, st));
+            S.launches23 += 1;
+            S.bytes23 += (double)n * cols * L.elem + matrix_bytes(A, L.elem);
+            nwg = kResidentParts;
+        } else if (D) {
             if (grid.parts > L.nwg_dot) return fail(LD_EINVAL, "internal: dot partials overflow");
             const int h = (m + 1) / 2;
             FusedBlock work[2] = {FusedBlock::chunks(S.W0, n, (int)L.elem), FusedBlock::chunks(S.W1, n, (int)L.elem)};
@@ -1568,6 +1612,9 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
                double* out_logdet, void* grad, ld_stats* stats, bool timed = true) {
     const auto t0 = std::chrono::steady_clock::now();
     const bool want_grad = grad != nullptr;
+    const char* prof = std::getenv("LD_PROFILE");
+    const bool print = prof && prof[0] && std::strcmp(prof, "0") != 0;
+    timed = timed && (stats || print);   // no events that nobody reads
     EstimateState S;
     S.timed = timed;
     LD_CHECK(make_plan(lmin, lmax, degree, o, S.plan));
@@ -1611,11 +1658,11 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
     }
     if (ar.base && ar.used > layout_bytes(S.L, want_grad))
         return fail(LD_EINVAL, "internal: workspace layout overflow");
-    if (!o.trusted_csr) LD_CHECK(validate_csr(A, S.flag, st));
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
     if (!want_grad) {
         LD_CHECK(fit_blocks(A, degree, n_matvec, o, S.longrows, S.L));
-        S.fused_D = fused_line(A, S.longrows);
+        S.resident = resident_fits(A, S.longrows, o, degree);
+        S.fused_D = S.resident ? 0 : fused_line(A, S.longrows);
         if (S.fused_D) {
             // every block's quadratic forms or none: their coefficients are shared
             const FusedArgs f = fused_args(A, S.longrows, S.fused, STEP_DOT_SQ, (degree + 1) / 2, S.L.X.bw, S.fused_D);
@@ -1665,8 +1712,6 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
     *out_logdet = tot.value();
     LD_CHECK_HIP(hipStreamSynchronize(st));
     // statistics: to the caller, and one line on stderr when LD_PROFILE is set
-    const char* prof = std::getenv("LD_PROFILE");
-    const bool print = prof && prof[0] && std::strcmp(prof, "0") != 0;
     if (stats || print) {
         ld_stats local;
         ld_stats* const out = stats ? stats : &local;
@@ -1864,13 +1909,35 @@ struct AdaptBufs {
 // step, after steps 1, 2, 4 and then every kAdaptPoll steps, and stops a
 // chunk once no column is active.  `launches` counts the Newton steps.
 int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, const void* V, int ld, int nc,
-                   void* P, int ldp, const AdaptBufs& b, const LongRows& lr, hipStream_t st,
+                   void* P, int ldp, const AdaptBufs& b, const LongRows& lr, bool resident, hipStream_t st,
                    std::vector<int>& hdeg, int* launches) {
     const bool f64 = A->dtype == LD_F64;
     const size_t elem = f64 ? 8 : 4;
     const int n = (int)A->n;
     const int nwg_max = step_num_wg_any(n);
     const int m = p.degree;
+    if (resident) {   // the whole loop in one launch, no polling
+        ResidentArgs f{};
+        f.kind = STEP_ACC_NORM;
+        f.cols = nc;
+        f.steps = m;
+        f.src = V;
+        f.src_ld = ld;
+        f.out = P;
+        f.out_ld = ldp;
+        f.tol = tol;
+        f.deg = b.deg;
+        f.alpha = p.alpha;
+        f.init = p.d[0] + shift;
+        f.beta = p.beta.data();
+        f.d = p.d.data();
+        LD_CHECK_HIP(launch_resident(f64, dev_of(A), f, st));
+        hdeg.assign((size_t)nc, 0);
+        LD_CHECK_HIP(hipMemcpyAsync(hdeg.data(), b.deg, (size_t)nc * 4, hipMemcpyDeviceToHost, st));
+        LD_CHECK_HIP(hipStreamSynchronize(st));
+        if (launches) *launches += *std::max_element(hdeg.begin(), hdeg.end()) > 0 ? 1 : 0;
+        return LD_OK;
+    }
     const std::vector<int> deg0((size_t)nc, m);   // columns that never meet tol stop at the cap
     LD_CHECK_HIP(hipMemcpyAsync(b.deg, deg0.data(), (size_t)nc * 4, hipMemcpyHostToDevice, st));
     const uint64_t all = ~0ull;
@@ -1982,9 +2049,9 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     b.deg = (int*)ar.take(256);   // one block's columns (at most 64)
     if (ar.base && ar.used > adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o))
         return fail(LD_EINVAL, "internal: workspace layout overflow");
-    if (!o.trusted_csr) LD_CHECK(validate_csr(A, S.flag, st));
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
-    Timer tm(st, true);
+    S.resident = resident_fits(A, S.longrows, o, max_degree);
+    Timer tm(st, stats != nullptr);
     tm.mark();
     std::vector<int> deg_all((size_t)n_matvec, 0), hdeg;
     // ---- step 3: Y = F S column block by column block; S written out in Q1's block
@@ -1998,7 +2065,7 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
         else
             LD_CHECK_HIP(launch_fill_signs(f64, n, cols, L.Q1.ld, gcol, (const uint64_t*)S.mask, 1.0, sblk, st));
         LD_CHECK(adaptive_apply(A, S.plan, tol, 0.0, sblk, L.Q1.ld, cols, L.Y.block(blk), L.Y.ld, b, S.longrows,
-                                st, hdeg, &S.launches1));
+                                S.resident, st, hdeg, &S.launches1));
         for (int c = 0; c < cols; ++c) deg_all[(size_t)(gcol + c)] = hdeg[(size_t)c];
     }
     tm.mark();
@@ -2010,7 +2077,7 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     for (int blk = 0; blk < L.X.nblocks(); ++blk) {
         const int cols = L.X.bcols(blk), gcol = blk * L.X.bw;
         LD_CHECK(adaptive_apply(A, S.plan, tol, 0.0, L.X.block(blk), L.X.ld, cols, PX.block(blk), L.X.ld, b,
-                                S.longrows, st, hdeg, &S.launches23));
+                                S.longrows, S.resident, st, hdeg, &S.launches23));
         for (int c = 0; c < cols; ++c) deg_all[(size_t)(L.k + gcol + c)] = hdeg[(size_t)c];
         LD_CHECK(cross_product(f64, n, L.X.block(blk), Blk::plain(L.X.ld), cols, PX.block(blk), Blk::plain(L.X.ld),
                                cols, nullptr, b.gpart, b.sums, st));
@@ -2125,13 +2192,29 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
     void* const B0 = ar.take(room ? pblk : blk);
     void* const B1 = ar.take(room ? pblk : blk);
     void* const B2 = room ? ar.take(pblk) : nullptr;
-    int* flag = (int*)ar.take(256);
-    if (!o.trusted_csr) LD_CHECK(validate_csr(A, flag, st));
+    (void)ar.take(256);
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
     const int m = p.degree;
     const double d0 = p.d[0] + std::log(p.sigma);
-    if (const int D = room && o.block_cols <= 0 ? fused_line(A, lr) : 0) {
+    if (resident_fits(A, lr, o, m)) {
+        ResidentArgs f{};
+        f.kind = STEP_HORNER_VEC;
+        f.cols = nc;
+        f.steps = m;
+        f.src = V;
+        f.src_ld = nc;
+        f.out = PV;
+        f.out_ld = nc;
+        f.alpha = p.alpha;
+        f.init = p.d[m];
+        const std::vector<double> beta(p.beta.rbegin(), p.beta.rend());
+        std::vector<double> d(p.d.rbegin() + 1, p.d.rend());
+        d.back() = d0;
+        f.beta = beta.data();
+        f.d = d.data();
+        LD_CHECK_HIP(launch_resident(f64, dev_of(A), f, st));
+    } else if (const int D = room && o.block_cols <= 0 ? fused_line(A, lr) : 0) {
         // column groups whose V and two work blocks fit the Infinity Cache, each
         // through its whole recurrence; V's chunks are read by every launch
         const bool whole = nc == v && (uintptr_t)V % 16 == 0 && (uintptr_t)PV % 16 == 0;   // V is one chunk already
@@ -2225,12 +2308,12 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     b.sums = (double*)ar.take(64 * 64 * 8);
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take((size_t)nc * 4);
-    int* flag = (int*)ar.take(256);
-    if (!o.trusted_csr) LD_CHECK(validate_csr(A, flag, st));
+    (void)ar.take(256);
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
     std::vector<int> hdeg;
-    LD_CHECK(adaptive_apply(A, p, tol, std::log(p.sigma), V, nc, nc, PV, nc, b, lr, st, hdeg, nullptr));
+    LD_CHECK(adaptive_apply(A, p, tol, std::log(p.sigma), V, nc, nc, PV, nc, b, lr,
+                            resident_fits(A, lr, o, p.degree), st, hdeg, nullptr));
     if (degrees)
         for (int c = 0; c < nc; ++c) degrees[c] = hdeg[(size_t)c];
     return LD_OK;
@@ -2308,7 +2391,8 @@ int ld_spectral_bounds(const ld_csr* A, int32_t lanczos_steps, void* stream, dou
     char* const base = (char*)own.p;
     LD_CHECK_HIP(hipMemsetAsync(base, 0, 16, st));
     LD_CHECK_HIP(launch_validate_csr(dev_of(A), (int*)base, st));
-    LD_CHECK_HIP(launch_gershgorin(A->dtype == LD_F64, dev_of(A), (double*)(base + kAlign), (double*)(base + 16), st));
+    LD_CHECK_HIP(launch_gershgorin(A->dtype == LD_F64, dev_of(A), (const int*)base, (double*)(base + kAlign),
+                                   (double*)(base + 16), st));
     struct {
         int flag[4];
         double lo, hi;

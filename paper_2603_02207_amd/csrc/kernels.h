@@ -194,6 +194,38 @@ struct FusedGrid {
 FusedGrid fused_grid(int n, int D, int bcols, int elem, int levels, int max_parts);
 hipError_t launch_fused(bool f64, const FusedArgs& f, hipStream_t st);
 
+// Whole recurrences of a matrix whose CSR arrays and one 16-byte column chunk fit
+// a CU's LDS (resident.hip): `steps` steps w -> alpha*A*w - beta[j]*w (+ dj*S or
+// + dj*V, d[j] in step order) of every chunk of a row-major block of `cols`
+// columns, one workgroup per chunk.
+//   STEP_HORNER_SIGNS / _VEC: from init*S / init*V (V = src) to out
+//   STEP_DOT_SQ:   from src; step j's <in,out>, <out,out> to slots 2j+1, 2j+2 of
+//                  part, the first <in,in> to slot 0: kResidentParts partial rows
+//   STEP_ACC_NORM: Alg. 2's loop on the columns of src: out = init*v + sum_{m>=1}
+//                  d[m]*w_m, each column to the first m with |d[m]| ||w_m|| <= tol
+//                  (deg[c] = m) or `steps`
+constexpr int kResidentSteps = 200;
+constexpr int kResidentParts = 16;
+constexpr int kResidentLds = 156 << 10;   // of a CU's 160 KB
+struct ResidentArgs {
+    int kind, cols, steps;
+    const void* src;
+    int src_ld;
+    void* out;
+    int out_ld;
+    const uint64_t* mask;
+    int gcol;
+    double* part;
+    long long slot_stride;
+    int part_ld;
+    double tol;
+    int* deg;
+    double alpha, init;
+    const double *beta, *d;   // host
+};
+size_t resident_lds(long long n, long long nnz, int elem);
+hipError_t launch_resident(bool f64, const CsrDev& A, const ResidentArgs& f, hipStream_t st);
+
 // Sign mask of stream `key`: bit c of word r = (probe(r, c) == -1), c < k <= 64.
 // With `planes` non-null also its eight byte planes: planes[p*n + r] = byte p
 // of word r (8n bytes).
@@ -251,10 +283,10 @@ hipError_t launch_rowmat(bool f64, int n, const void* Y, Blk by, int ky, const d
 hipError_t launch_validate_csr(const CsrDev& A, int* flag, hipStream_t st);
 
 // Gershgorin: (min(a_ii - r_i), max(a_ii + r_i)) into out[0..2); part: 2 *
-// gersh_num_wg(n) doubles.  Reads nothing out of range whatever the CSR arrays
-// hold (the result then means nothing).
+// gersh_num_wg(n) doubles; check: launch_validate_csr's flags (nothing is read
+// of a matrix that failed, and the result then means nothing).
 int gersh_num_wg(int n);
-hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, double* out, hipStream_t st);
+hipError_t launch_gershgorin(bool f64, const CsrDev& A, const int* check, double* part, double* out, hipStream_t st);
 
 // Gradient sweep step (all blocks n x ld row-major, ncols used; grad FP64):
 //   grad[nz(r,c)] (+)= alpha * sum_cols own[r, col] * w[c, col]
@@ -340,6 +372,10 @@ constexpr int kFarInfo = 10;
 constexpr int kBandInfo = 16;
 constexpr int kConstFlag = 13;
 constexpr int kConstInfo = 32;   // int index; 8-byte aligned doubles
+// further slots of the block, filled by other launches: the CSR check's two flags
+// (launch_validate_csr) and the long rows' count (launch_long_rows)
+constexpr int kCheckInfo = 56;
+constexpr int kLongInfo = 58;
 hipError_t launch_rows_probe(bool f64, const CsrDev& A, int* info, hipStream_t st);
 hipError_t launch_dia_build(bool f64, const CsrDev& A, void* dia, uint16_t* pres, int* info, hipStream_t st);
 

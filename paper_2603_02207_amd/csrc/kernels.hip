@@ -2125,7 +2125,8 @@ hipError_t launch_validate_csr(const CsrDev& A, int* flag, hipStream_t st) {
 // Gershgorin discs
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(kThreads) void gersh_kernel(int n, int nnz, const int* __restrict__ row_ptr,
+__global__ __launch_bounds__(kThreads) void gersh_kernel(int n, const int* __restrict__ check,
+                                                         const int* __restrict__ row_ptr,
                                                          const int* __restrict__ col_idx,
                                                          const T* __restrict__ val,
                                                          double* __restrict__ part) {
@@ -2133,8 +2134,9 @@ __global__ __launch_bounds__(kThreads) void gersh_kernel(int n, int nnz, const i
     double lo = __builtin_inf(), hi = -__builtin_inf();
     if (r < n) {
         double diag = 0.0, rad = 0.0;
-        const int end = min(row_ptr[r + 1], nnz);
-        for (int k = max(row_ptr[r], 0); k < end; ++k) {
+        const bool valid = check[0] == 0 && check[1] == 0;   // else nothing is read
+        const int end = valid ? row_ptr[r + 1] : 0;
+        for (int k = valid ? row_ptr[r] : 0; k < end; ++k) {
             const double v = (double)val[k];
             if (col_idx[k] == r)
                 diag += v;
@@ -2188,14 +2190,15 @@ __global__ __launch_bounds__(kThreads) void gersh_total_kernel(int wgs, const do
     }
 }
 
-hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, double* out, hipStream_t st) {
+hipError_t launch_gershgorin(bool f64, const CsrDev& A, const int* check, double* part, double* out,
+                             hipStream_t st) {
     const int nwg = gersh_num_wg(A.n);
     if (nwg == 0) return hipSuccess;
     if (f64)
-        hipLaunchKernelGGL(gersh_kernel<double>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr,
+        hipLaunchKernelGGL(gersh_kernel<double>, dim3(nwg), dim3(kThreads), 0, st, A.n, check, A.row_ptr,
                            A.col_idx, (const double*)A.val, part);
     else
-        hipLaunchKernelGGL(gersh_kernel<float>, dim3(nwg), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr,
+        hipLaunchKernelGGL(gersh_kernel<float>, dim3(nwg), dim3(kThreads), 0, st, A.n, check, A.row_ptr,
                            A.col_idx, (const float*)A.val, part);
     hipLaunchKernelGGL(gersh_total_kernel, dim3(1), dim3(kThreads), 0, st, nwg, part, out);
     return hipGetLastError();
@@ -2204,14 +2207,16 @@ hipError_t launch_gershgorin(bool f64, const CsrDev& A, double* part, double* ou
 // Candidate diagonals: the distinct offsets col - row of 64 rows scattered
 // over the matrix, merged in ascending order by one lane; info[0] = their number,
 // or -1 when a sampled row or the union exceeds kMaxDiag.
-__global__ __launch_bounds__(64) void dia_probe_kernel(int n, const int* __restrict__ row_ptr,
+// (The row bounds are clamped to the arrays: the check of the CSR structure is
+// read back together with this.)
+__global__ __launch_bounds__(64) void dia_probe_kernel(int n, int nnz, const int* __restrict__ row_ptr,
                                                        const int* __restrict__ col_idx, const void* __restrict__ val,
                                                        int f64, int* __restrict__ info) {
     // one wave: lane t samples one row (golden-ratio stride: no alignment with
     // a grid's rows, whatever its width) and holds its column offsets
     const int t = threadIdx.x;
     const int r = (int)(((uint64_t)(t + 1) * 0x9E3779B97F4A7C15ull) % (uint64_t)n);
-    const int b = row_ptr[r], e = row_ptr[r + 1];
+    const int b = min(max(row_ptr[r], 0), nnz), e = min(max(row_ptr[r + 1], b), nnz);
     const bool fits = e - b <= kMaxDiag;
     int off[kMaxDiag];
 #pragma unroll
@@ -2289,7 +2294,7 @@ __global__ __launch_bounds__(64) void dia_probe_kernel(int n, const int* __restr
 constexpr int kDiaFlag = 12;
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void dia_build_kernel(int n, const int* __restrict__ row_ptr,
+__global__ __launch_bounds__(kThreads) void dia_build_kernel(int n, int nnz, const int* __restrict__ row_ptr,
                                                              const int* __restrict__ col_idx,
                                                              const T* __restrict__ val, T* __restrict__ dia,
                                                              uint16_t* __restrict__ pres, int* __restrict__ info) {
@@ -2318,7 +2323,13 @@ __global__ __launch_bounds__(kThreads) void dia_build_kernel(int n, const int* _
         }
         bool bad = false, varies = false;
         unsigned bits = 0;
-        for (int k = row_ptr[r]; k < row_ptr[r + 1]; ++k) {
+        const int first = max(row_ptr[r], 0);
+        int last = min(row_ptr[r + 1], nnz);
+        if (last - first > kMaxDiag) {   // some entry lies on no candidate
+            bad = true;
+            last = first;
+        }
+        for (int k = first; k < last; ++k) {
             const int o = col_idx[k] - r;
             const T x = val[k];
             bool hit = false;
@@ -2346,7 +2357,7 @@ __global__ __launch_bounds__(kThreads) void dia_build_kernel(int n, const int* _
 
 hipError_t launch_rows_probe(bool f64, const CsrDev& A, int* info, hipStream_t st) {
     if (A.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(dia_probe_kernel, dim3(1), dim3(64), 0, st, A.n, A.row_ptr, A.col_idx, A.val, (int)f64, info);
+    hipLaunchKernelGGL(dia_probe_kernel, dim3(1), dim3(64), 0, st, A.n, A.nnz, A.row_ptr, A.col_idx, A.val, (int)f64, info);
     return hipGetLastError();
 }
 
@@ -2354,10 +2365,10 @@ hipError_t launch_dia_build(bool f64, const CsrDev& A, void* dia, uint16_t* pres
     if (A.n == 0) return hipSuccess;
     const int nb = div_up(A.n, kThreads);
     if (f64)
-        hipLaunchKernelGGL(dia_build_kernel<double>, dim3(nb), dim3(kThreads), 0, st, A.n, A.row_ptr, A.col_idx,
+        hipLaunchKernelGGL(dia_build_kernel<double>, dim3(nb), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr, A.col_idx,
                            (const double*)A.val, (double*)dia, pres, info);
     else
-        hipLaunchKernelGGL(dia_build_kernel<float>, dim3(nb), dim3(kThreads), 0, st, A.n, A.row_ptr, A.col_idx,
+        hipLaunchKernelGGL(dia_build_kernel<float>, dim3(nb), dim3(kThreads), 0, st, A.n, A.nnz, A.row_ptr, A.col_idx,
                            (const float*)A.val, (float*)dia, pres, info);
     return hipGetLastError();
 }
