@@ -1880,16 +1880,10 @@ int lanczos_upper(const ld_csr* A, int steps, double abs_bound, char* base, hipS
 
 // Workspace of the adaptive apply: two n x ncols blocks, step partials for
 // 64 columns, Gram partials, small sums, the mask, degrees, flag, long rows.
+// Chunked: and the blocks of the launches of several steps.
 constexpr int kAdaptPoll = 8;   // steps between host checks of the active mask (after the first few)
+constexpr size_t kPackMost = (size_t)4 << 30;   // bytes of a block that is copied to another layout, at most
 
-size_t adaptive_ws_bytes(const ld_csr* A, int ncols, const ld_options& o) {
-    const size_t elem = A->dtype == LD_F64 ? 8 : 4;
-    const int n = (int)A->n;
-    return 2 * align_up((size_t)n * ncols * elem) +
-           align_up((size_t)step_num_wg_any(n) * 64 * 8) +
-           align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + align_up(256) +
-           align_up((size_t)ncols * 4) + align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
-}
 
 // Buffers of Alg. 2's adaptive loop: two n x ld temporaries (ld of the
 // input), step partials (step_num_wg_any(n) x 64 doubles), Gram partials
@@ -1897,9 +1891,121 @@ size_t adaptive_ws_bytes(const ld_csr* A, int ncols, const ld_options& o) {
 struct AdaptBufs {
     void* W[2] = {nullptr, nullptr};
     double *part = nullptr, *gpart = nullptr, *sums = nullptr;
-    uint64_t* mask = nullptr;
+    uint64_t* mask = nullptr;          // kAdaptWords words and, after them, the redo flag
     int* deg = nullptr;
+    // launches of several steps: two vectors and two accumulators of up to 64
+    // columns in 16-byte chunks (null: no room, one launch per step)
+    void* chunks[4] = {nullptr, nullptr, nullptr, nullptr};
 };
+static_assert(kAdaptWords * 8 + 4 <= 256, "the mask's 256 bytes");
+
+// Bytes of one of adaptive_fused's four blocks of chunks; 0 when the matrix
+// cannot qualify or a block would be beyond kPackMost (no room is asked for).
+size_t adaptive_chunk_bytes(const ld_csr* A, int ncols) {
+    const size_t elem = A->dtype == LD_F64 ? 8 : 4;
+    const size_t blk = align_up((size_t)A->n * padded_ld(std::min(ncols, 64), (int)elem) * elem);
+    return A->n > kFusedMinWidth && A->nnz <= 5 * A->n && blk <= kPackMost ? blk : 0;
+}
+
+// Takes them from the workspace (which has room); W0 and W1 serve as two of
+// them where they are long enough.
+void take_chunks(Arena& ar, const ld_csr* A, int ncols, size_t wbytes, AdaptBufs& b) {
+    const size_t blk = adaptive_chunk_bytes(A, ncols);
+    if (blk == 0) return;
+    for (int i = 0; i < 4; ++i) b.chunks[i] = i < 2 && wbytes >= blk ? b.W[i] : ar.take(blk);
+}
+
+size_t adaptive_ws_bytes(const ld_csr* A, int ncols, const ld_options& o, bool chunked) {
+    const size_t elem = A->dtype == LD_F64 ? 8 : 4;
+    const int n = (int)A->n;
+    const size_t w = align_up((size_t)n * ncols * elem), chunk = adaptive_chunk_bytes(A, ncols);
+    return (chunked ? (w >= chunk ? 2 : 4) * chunk : 0) + 2 * w +
+           align_up((size_t)step_num_wg_any(n) * 64 * 8) +
+           align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + align_up(256) +
+           align_up((size_t)ncols * 4) + align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+}
+
+// adaptive_fused's launches on qc columns, and whether their partial sums have
+// room (lines so long that few of them make the matrix have too many strips).
+FusedArgs adaptive_args(const ld_csr* A, const FusedPlan& q, int qc, int D, const AdaptBufs& b, const LongRows& lr) {
+    FusedArgs f = fused_args(A, lr, q, STEP_ACC_NORM, (int)q.mid.size(), qc, D);
+    f.part = b.part;
+    f.part_ld = padded_ld(qc, A->dtype == LD_F64 ? 8 : 4);
+    f.max_parts = (int)((size_t)step_num_wg_any((int)A->n) * 64 / ((size_t)f.grid_levels * f.part_ld));
+    return f;
+}
+bool adaptive_fits(const ld_csr* A, const FusedPlan& q, int qc, int D, const AdaptBufs& b, const LongRows& lr) {
+    const FusedArgs f = adaptive_args(A, q, qc, D, b, lr);
+    return f.max_parts > 0 &&
+           fused_grid(f.n, D, qc, A->dtype == LD_F64 ? 8 : 4, f.grid_levels, f.max_parts).parts <= f.max_parts;
+}
+
+// Alg. 2's loop on up to 64 columns of a five-point stencil, several steps per
+// launch (from degree 0, whose test has set the mask; every result of P is
+// written here).  A launch takes its levels for every column that is active when
+// it starts; the test of all its levels follows, and when some column stopped
+// before the last of them the launch is repeated with each level's own columns.
+// The repeat is always queued and returns at once unless it is wanted, as every
+// launch does once no column is active, so the host may run ahead: it polls the
+// mask after the first launch and then after every second one.
+// Measured (gfx950, FP32, 2048^2, 32 queries, about 49 steps): a launch of four
+// steps 290 us against 4 x (267 + 15) us one step at a time; the estimate 30.0 ->
+// 11.7 ms.  Short loops gain too (2..11 steps at 1024^2, 16 queries: 1.3 ms).
+int adaptive_fused(const ld_csr* A, const FusedPlan& q, double tol, double shift, const void* V, int ld, int qc,
+                   void* P, int ldp, int D, const AdaptBufs& b, int* deg, const LongRows& lr, hipStream_t st,
+                   int* launches) {
+    const bool f64 = A->dtype == LD_F64;
+    const int elem = f64 ? 8 : 4, n = (int)A->n, m = (int)q.mid.size(), v = 16 / elem;
+    uint64_t* const words = b.mask;
+    int* const redo = (int*)(words + kAdaptWords);
+    FusedArgs f = adaptive_args(A, q, qc, D, b, lr);
+    const int parts = fused_grid(n, D, qc, elem, f.grid_levels, f.max_parts).parts;
+    f.slot_stride = (long long)parts * f.part_ld;
+    FusedBlock in = FusedBlock::rows(const_cast<void*>(V), ld, elem);
+    if (ld % v != 0 || (uintptr_t)V % 16 != 0) {   // the second launch is the first to write chunks[1]
+        LD_CHECK_HIP(launch_pack_chunks(f64, n, qc, V, ld, b.chunks[1], st));
+        in = FusedBlock::chunks(b.chunks[1], n, elem);
+    }
+    AdaptLevels lv{};
+    LD_CHECK_HIP(launch_adapt_decide_levels(b.sums, 0, qc, lv, 0, tol, 0, words, redo, deg, st));   // words[kAdaptNext..]
+    int cur = 0, done = 0;
+    uint64_t h[kAdaptWords] = {};
+    for (int i = 0; done < m; ++i) {
+        f.levels = fused_next(f, m - done);
+        f.init = done == 0;
+        f.init_scale = q.d[0] + shift;
+        set_in(f, in);
+        set_out(f, FusedBlock::chunks(b.chunks[cur], n, elem));
+        f.pin = b.chunks[3 - cur];
+        f.pout = b.chunks[2 + cur];
+        for (int t = 0; t < f.levels; ++t) {
+            f.mid[t] = q.mid[done + t];
+            f.nbeta[t] = q.nbeta[done + t];
+            f.dj[t] = q.d[done + t + 1];
+            lv.dm_abs[t] = std::fabs(q.d[done + t + 1]);
+        }
+        f.active = words + kAdaptNext;
+        f.run = nullptr;
+        LD_CHECK_HIP(launch_fused(f64, f, st));
+        LD_CHECK_HIP(launch_reduce(b.part, parts, qc, f.part_ld, f.levels, f.slot_stride, b.sums, 64, st));
+        LD_CHECK_HIP(launch_adapt_decide_levels(b.sums, 64, qc, lv, f.levels, tol, done, words, redo, deg, st));
+        f.active = words + 1;
+        f.run = redo;
+        LD_CHECK_HIP(launch_fused(f64, f, st));
+        in = FusedBlock::chunks(b.chunks[cur], n, elem);
+        cur = 1 - cur;
+        done += f.levels;
+        if (i % 2 == 0 || done == m) {
+            LD_CHECK_HIP(hipMemcpyAsync(h, words, sizeof(h), hipMemcpyDeviceToHost, st));
+            LD_CHECK_HIP(hipStreamSynchronize(st));
+            if (h[0] == 0) break;
+        }
+    }
+    const int ran = (int)h[kAdaptRan];   // launches that found an active column
+    if (launches) *launches += ran;
+    LD_CHECK_HIP(launch_unpack_chunks(f64, n, qc, b.chunks[2 + (ran - 1) % 2], P, ldp, st));
+    return LD_OK;
+}
 
 // Alg. 2 with each column's own stopping rule on the n x nc block V (leading
 // dimension ld) into P (leading dimension ldp): column c starts with w_0 = v,
@@ -1938,6 +2044,9 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
         if (launches) *launches += *std::max_element(hdeg.begin(), hdeg.end()) > 0 ? 1 : 0;
         return LD_OK;
     }
+    const int D = b.chunks[0] ? fused_line(A, lr) : 0;
+    FusedPlan fp;
+    if (D) fp = fused_plan(A, lr, p);
     const std::vector<int> deg0((size_t)nc, m);   // columns that never meet tol stop at the cap
     LD_CHECK_HIP(hipMemcpyAsync(b.deg, deg0.data(), (size_t)nc * 4, hipMemcpyHostToDevice, st));
     const uint64_t all = ~0ull;
@@ -1947,8 +2056,6 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
         const int qc = std::min(64, nc - q0);
         const uint8_t* Vq = v8 + (size_t)q0 * elem;
         uint8_t* Pq = p8 + (size_t)q0 * elem;
-        // P_0 = (d_0 + shift) w_0, w_0 = v
-        LD_CHECK_HIP(launch_scale_copy(f64, n, qc, Vq, ld, p.d[0] + shift, Pq, ldp, st));
         // e_0 = |d_0| ||v||: the diagonal of the chunk's Gram matrix
         LD_CHECK(cross_product(f64, n, Vq, Blk::plain(ld), qc, Vq, Blk::plain(ld), qc, nullptr, b.gpart, b.sums,
                                st));
@@ -1958,6 +2065,12 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
             uint64_t h = 0;
             LD_CHECK_HIP(hipMemcpyAsync(&h, b.mask, 8, hipMemcpyDeviceToHost, st));
             LD_CHECK_HIP(hipStreamSynchronize(st));
+            if (h != 0 && D && adaptive_fits(A, fp, qc, D, b, lr)) {
+                LD_CHECK(adaptive_fused(A, fp, tol, shift, Vq, ld, qc, Pq, ldp, D, b, b.deg + q0, lr, st, launches));
+                continue;
+            }
+            // P_0 = (d_0 + shift) w_0, w_0 = v
+            LD_CHECK_HIP(launch_scale_copy(f64, n, qc, Vq, ld, p.d[0] + shift, Pq, ldp, st));
             if (h == 0) continue;
         }
         const uint8_t* cur = Vq;
@@ -2012,10 +2125,11 @@ EstLayout layout_adaptive(const ld_csr* A, int max_degree, int n_matvec, const l
     return layout_estimate(A, max_degree, n_matvec, false, o, matrix_bytes(A, A->dtype == LD_F64 ? 8 : 4));
 }
 
-size_t adaptive_estimate_ws_bytes(const ld_csr* A, int max_degree, int n_matvec, const ld_options& o) {
+size_t adaptive_estimate_ws_bytes(const ld_csr* A, int max_degree, int n_matvec, const ld_options& o, bool chunked) {
     const EstLayout L = layout_adaptive(A, max_degree, n_matvec, o);
     const int n = (int)A->n;
-    return layout_bytes(L, false) + align_up(L.xb) + align_up((size_t)step_num_wg_any(n) * 64 * 8) +
+    const size_t chunk = chunked ? adaptive_chunk_bytes(A, std::max(L.Y.bw, L.X.bw)) : 0;
+    return layout_bytes(L, false) + (L.W >= chunk ? 2 : 4) * chunk + align_up(L.xb) + align_up((size_t)step_num_wg_any(n) * 64 * 8) +
            align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + 2 * align_up(256) + 256;
 }
 
@@ -2034,7 +2148,10 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     S.probe = o.probe_dist;
     OwnedWs own;
     Arena ar;
-    LD_CHECK(get_workspace(workspace, ws_bytes, adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o), own, ar));
+    // a workspace without the blocks of chunks takes one launch per step
+    const size_t plain = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, false);
+    const size_t with_chunks = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, true);
+    LD_CHECK(get_workspace(workspace, ws_bytes, workspace ? plain : with_chunks, own, ar));
     carve(ar, S.L, S);
     const EstLayout& L = S.L;
     BlkMat PX = L.X;   // F [Q_b | U], the layout of X
@@ -2047,8 +2164,8 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     b.sums = (double*)ar.take(64 * 64 * 8);
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take(256);   // one block's columns (at most 64)
-    if (ar.base && ar.used > adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o))
-        return fail(LD_EINVAL, "internal: workspace layout overflow");
+    if (ar.used > plain) return fail(LD_EINVAL, "internal: workspace layout overflow");
+    if (ar.size >= with_chunks) take_chunks(ar, A, std::max(L.Y.bw, L.X.bw), L.W, b);
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
     S.resident = resident_fits(A, S.longrows, o, max_degree);
     Timer tm(st, stats != nullptr);
@@ -2129,7 +2246,6 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
 // Workspace of ld_apply_log: two blocks as V is stored, or, packed, V and two
 // blocks with rows padded to whole 16-byte vectors (not asked for above
 // kPackMost bytes a block).
-constexpr size_t kPackMost = (size_t)4 << 30;
 
 size_t apply_ws_bytes(const ld_csr* A, int64_t ncols, const ld_options& o, bool packed) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4, v = 16 / elem;
@@ -2149,7 +2265,7 @@ int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t
     if (degree < 1) return fail(LD_EINVAL, "degree must be >= 1");
     const ld_options o = resolve(opts);
     if (n_matvec < 0 && want_grad) {
-        *bytes = adaptive_ws_bytes(A, (int)(-(int64_t)n_matvec), o);
+        *bytes = adaptive_ws_bytes(A, (int)(-(int64_t)n_matvec), o, true);
         return LD_OK;
     }
     if (n_matvec < 0) {
@@ -2218,7 +2334,7 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
         // column groups whose V and two work blocks fit the Infinity Cache, each
         // through its whole recurrence; V's chunks are read by every launch
         const bool whole = nc == v && (uintptr_t)V % 16 == 0 && (uintptr_t)PV % 16 == 0;   // V is one chunk already
-        if (!whole) LD_CHECK_HIP(launch_pack_chunks(f64, n, nc, V, B2, st));
+        if (!whole) LD_CHECK_HIP(launch_pack_chunks(f64, n, nc, V, nc, B2, st));
         const double per_chunk = 3.0 * 16.0 * (double)n;
         const FusedPlan fp = fused_plan(A, lr, p);
         const int group = std::max(1, (int)(kBlockPairBudget / per_chunk)) * v;
@@ -2239,7 +2355,7 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
             LD_CHECK(fused_horner(A, fp, f, std::log(p.sigma),
                                   FusedBlock::chunks(whole ? PV : (char*)B0 + at, n, (int)elem), W0, W1, st, &launches));
         }
-        if (!whole) LD_CHECK_HIP(launch_unpack_chunks(f64, n, nc, B0, PV, st));
+        if (!whole) LD_CHECK_HIP(launch_unpack_chunks(f64, n, nc, B0, PV, nc, st));
     } else {
         // Rows of V that are no whole number of 16-byte vectors (three columns or
         // more: fewer move less as they are) go through padded copies: the steps'
@@ -2299,7 +2415,8 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     if (v8 < p8 + blk && p8 < v8 + blk) return fail(LD_EINVAL, "V and PV overlap");
     OwnedWs own;
     Arena ar;
-    LD_CHECK(get_workspace(workspace, ws_bytes, adaptive_ws_bytes(A, nc, o), own, ar));
+    const size_t with_chunks = adaptive_ws_bytes(A, nc, o, true);   // without: one launch per step
+    LD_CHECK(get_workspace(workspace, ws_bytes, workspace ? adaptive_ws_bytes(A, nc, o, false) : with_chunks, own, ar));
     AdaptBufs b;
     b.W[0] = ar.take(blk);
     b.W[1] = ar.take(blk);
@@ -2309,6 +2426,7 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take((size_t)nc * 4);
     (void)ar.take(256);
+    if (ar.size >= with_chunks) take_chunks(ar, A, nc, align_up(blk), b);
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
     std::vector<int> hdeg;
@@ -2326,7 +2444,7 @@ int ld_adaptive_workspace_size(const ld_csr* A, int32_t max_degree, int32_t n_ma
     LD_CHECK(check_csr_args(A));
     if (max_degree < 1) return fail(LD_EINVAL, "max_degree must be >= 1");
     if (n_matvec < 3) return fail(LD_EINVAL, "n_matvec must be >= 3");
-    *bytes = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, resolve(opts));
+    *bytes = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, resolve(opts), true);
     return LD_OK;
 }
 

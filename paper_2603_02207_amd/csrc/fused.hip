@@ -86,7 +86,11 @@ struct FusedDev {
     long long slot_stride;
     int part_ld, bcols;
     int store, nt_out;
-    T init;                    // INIT: level 0 = init * S (or V)
+    const T* pin;              // ACC: the accumulator, laid out as the output (win and wout too)
+    T* pout;
+    const uint64_t* active;    // ACC: the columns that accumulate level t's term, bit c of active[t]
+    const int* run;            // ACC: when non-null, the launch does nothing unless *run != 0
+    T init;                    // INIT: level 0 = init * S (or V); ACC: the accumulator = init * the input
     T c[5];                    // alpha * diagonal value (the centre's is in mid)
     T mid[kFusedMax], nbeta[kFusedMax], dj[kFusedMax];   // alpha * centre - beta, -beta
 };
@@ -122,9 +126,13 @@ __device__ __forceinline__ void add_shifted(double (&acc)[2], const double (&x)[
 
 template <typename T, int VEC, int KIND, int LV, bool INIT>
 __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
-    static_assert(KIND == STEP_HORNER_SIGNS || KIND == STEP_HORNER_VEC || KIND == STEP_DOT_SQ, "fused kinds");
+    static_assert(KIND == STEP_HORNER_SIGNS || KIND == STEP_HORNER_VEC || KIND == STEP_DOT_SQ || KIND == STEP_ACC_NORM,
+                  "fused kinds");
     constexpr bool kSigns = KIND == STEP_HORNER_SIGNS, kVec = KIND == STEP_HORNER_VEC, kDot = KIND == STEP_DOT_SQ;
+    constexpr bool kAcc = KIND == STEP_ACC_NORM, kSum = kDot || kAcc;
     constexpr bool kFirst = kDot && INIT;   // the sums of the input block too
+    constexpr bool kReadAcc = kAcc && !INIT;
+    if (kAcc && ((a.run && *a.run == 0) || a.active[0] == 0)) return;
     constexpr bool kReadIn = !(INIT && (kSigns || kVec));
     using P = Chunk<T, VEC>;
     const int lane = threadIdx.x & 63;
@@ -151,14 +159,23 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
     unsigned meta[LV + 1];         // line of level t: presence bits, and the chunk's sign bits at the top
     P vline[kVec ? LV + 1 : 1];    // VECS: V's line of level t
     unsigned full = 0;             // bit t: every lane of level t's line has all five entries
-    double s0[VEC], s1[kDot ? LV : 1][VEC], s2[kDot ? LV : 1][VEC];
+    P accl[kAcc ? LV + 1 : 1];     // ACC: the accumulator's line of level t
+    unsigned on[kAcc ? LV : 1];    // ACC: the chunk's columns that take level t + 1's term
+    double s0[VEC], s1[kDot ? LV : 1][VEC], s2[kSum ? LV : 1][VEC];
+    const long long pofs = (long long)q * a.wout_cs;
+#pragma unroll
+    for (int t = 0; t < (kAcc ? LV : 1); ++t) on[t] = kAcc ? (unsigned)(a.active[t] >> (q * VEC)) : 0u;   // q*VEC < 64
 #pragma unroll
     for (int t = 0; t <= LV; ++t) meta[t] = 0;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         s0[e] = 0.0;
 #pragma unroll
-        for (int t = 0; t < (kDot ? LV : 1); ++t) s1[t][e] = s2[t][e] = 0.0;
+        for (int t = 0; t < (kDot ? LV : 1); ++t) s1[t][e] = 0.0;
+#pragma unroll
+        for (int t = 0; t < (kSum ? LV : 1); ++t) s2[t][e] = 0.0;
+#pragma unroll
+        for (int t = 0; t < (kAcc ? LV + 1 : 1); ++t) accl[t].v[e] = T(0);
 #pragma unroll
         for (int t = 0; t < LV; ++t) ring[t][0].v[e] = ring[t][1].v[e] = ring[t][2].v[e] = T(0);
 #pragma unroll
@@ -166,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
     }
 
     // three lines in flight
-    P wf[kReadIn ? 3 : 1], vf[kVec ? 3 : 1];
+    P wf[kReadIn ? 3 : 1], vf[kVec ? 3 : 1], af[kReadAcc ? 3 : 1];
     unsigned pm[3], pb[3];
     const int iters = ny + 2 * LV;
     auto fetch = [&](int k, int s) __attribute__((always_inline)) {
@@ -175,11 +192,13 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
         for (int e = 0; e < VEC; ++e) {
             if (kReadIn) wf[kReadIn ? s : 0].v[e] = T(0);
             if (kVec) vf[kVec ? s : 0].v[e] = T(0);
+            if (kReadAcc) af[kReadAcc ? s : 0].v[e] = T(0);
         }
         pm[s] = pb[s] = 0;
         if (k < iters && (unsigned)r < (unsigned)a.n) {
             if (kReadIn) wf[kReadIn ? s : 0] = *reinterpret_cast<const P*>(win + (size_t)r * a.win_rs);
             if (kVec) vf[kVec ? s : 0] = *reinterpret_cast<const P*>(vsrc + (size_t)r * a.vsrc_rs);
+            if (kReadAcc) af[kReadAcc ? s : 0] = *reinterpret_cast<const P*>(a.pin + pofs + (size_t)r * a.wout_rs);
             pm[s] = a.pres[r];
             if (kSigns) pb[s] = plane[r];
         }
@@ -194,6 +213,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
         for (int t = LV; t >= 1; --t) {
             meta[t] = meta[t - 1];
             if (kVec) vline[kVec ? t : 0] = vline[kVec ? t - 1 : 0];
+            if (kAcc) accl[kAcc ? t : 0] = accl[kAcc ? t - 1 : 0];   // level t - 1's line of the iteration before
         }
         meta[0] = pm[S];
         if (kSigns) meta[0] |= (pb[S] >> pshift) << (32 - VEC);
@@ -204,6 +224,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
         for (int e = 0; e < VEC; ++e) {
             if (INIT && kSigns) ring[0][S].v[e] = with_sign(a.init, meta[0] << (VEC - 1 - e));
             if (INIT && kVec) ring[0][S].v[e] = a.init * vline[0].v[e];
+            if (kAcc) accl[0].v[e] = INIT ? a.init * wf[kReadIn ? S : 0].v[e] : af[kReadAcc ? S : 0].v[e];
         }
         fetch(k + 3, S);
 #pragma unroll
@@ -238,15 +259,17 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
             for (int e = 0; e < VEC; ++e) {
                 if (kSigns) o.v[e] += with_sign(a.dj[t - 1], meta[t] << (VEC - 1 - e));
                 if (kVec) o.v[e] = fma(a.dj[t - 1], vline[kVec ? t : 0].v[e], o.v[e]);
+                if (kAcc && ((on[kAcc ? t - 1 : 0] >> e) & 1u))
+                    accl[kAcc ? t : 0].v[e] = fma(a.dj[t - 1], o.v[e], accl[kAcc ? t : 0].v[e]);
             }
             const int ly = k - t - LV;   // the line's index among the wave's own
-            if (kDot && ly >= 0 && ly < ny && own) {
+            if (kSum && ly >= 0 && ly < ny && own) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     const double wd = (double)mid.v[e], od = (double)o.v[e];
                     if (kFirst && t == 1) s0[e] = fma(wd, wd, s0[e]);
-                    s1[kDot ? t - 1 : 0][e] = fma(wd, od, s1[kDot ? t - 1 : 0][e]);
-                    s2[kDot ? t - 1 : 0][e] = fma(od, od, s2[kDot ? t - 1 : 0][e]);
+                    if (kDot) s1[kDot ? t - 1 : 0][e] = fma(wd, od, s1[kDot ? t - 1 : 0][e]);
+                    s2[kSum ? t - 1 : 0][e] = fma(od, od, s2[kSum ? t - 1 : 0][e]);
                 }
             }
             if (t < LV) {
@@ -264,6 +287,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
                     } else {
                         *reinterpret_cast<P*>(dst) = o;
                     }
+                    if (kAcc) *reinterpret_cast<P*>(a.pout + pofs + (size_t)r * a.wout_rs) = accl[kAcc ? LV : 0];
                 }
             }
         }
@@ -277,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
     if (k < iters) iteration(k, std::integral_constant<int, 0>{});
     if (k + 1 < iters) iteration(k + 1, std::integral_constant<int, 1>{});
 
-    if constexpr (kDot) {   // butterfly over the wave, lane 0 writes the wave's partial row
+    if constexpr (kSum) {   // butterfly over the wave, lane 0 writes the wave's partial row
         const size_t at = (size_t)sc * a.part_ld + q * VEC;
         auto total = [&](double v, int slot, int e) __attribute__((always_inline)) {
 #pragma unroll
@@ -290,8 +314,8 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedDev<T> a) {
             if (kFirst) total(s0[e], 0, e);
 #pragma unroll
             for (int t = 0; t < LV; ++t) {
-                total(s1[t][e], base + 2 * t, e);
-                total(s2[t][e], base + 2 * t + 1, e);
+                if (kDot) total(s1[kDot ? t : 0][e], base + 2 * t, e);
+                total(s2[t][e], kDot ? base + 2 * t + 1 : t, e);
             }
         }
     }
@@ -348,6 +372,10 @@ hipError_t launch_fused_t(const FusedArgs& f, hipStream_t st) {
     d.bcols = f.bcols;
     d.store = f.wout != nullptr;
     d.nt_out = f.nt_out;
+    d.pin = (const T*)f.pin;
+    d.pout = (T*)f.pout;
+    d.active = f.active;
+    d.run = f.run;
     d.init = (T)f.init_scale;
     for (int q = 0; q < 5; ++q) d.c[q] = (T)f.off[q];
     for (int t = 0; t < f.levels; ++t) {
@@ -359,6 +387,9 @@ hipError_t launch_fused_t(const FusedArgs& f, hipStream_t st) {
         case STEP_HORNER_SIGNS: return launch_fused_k<T, STEP_HORNER_SIGNS>(d, f.levels, f.init, st);
         case STEP_HORNER_VEC: return launch_fused_k<T, STEP_HORNER_VEC>(d, f.levels, f.init, st);
         case STEP_DOT_SQ: return launch_fused_k<T, STEP_DOT_SQ>(d, f.levels, f.init, st);
+        case STEP_ACC_NORM:
+            if (!f.active || !f.pout || !f.wout) return hipErrorInvalidValue;
+            return launch_fused_k<T, STEP_ACC_NORM>(d, f.levels, f.init, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -140,6 +140,11 @@ hipError_t launch_step(bool f64, const CsrDev& A, const StepArgs& s, hipStream_t
 //                      2t, 2t+1 of part ([slot][partial row][part_ld]); with
 //                      init slot 0 takes <in,in> and the others move up by one.
 //                      wout null: the last vector is not written.
+//   STEP_ACC_NORM:     level t adds dj[t]*w to the accumulator on the columns of
+//                      active[t] (device words) and writes <out,out> to slot t;
+//                      pin to pout, laid out as the output; with init the
+//                      accumulator starts as init_scale*input.  run non-null: the
+//                      launch does nothing unless *run (device) is nonzero.
 //
 // Every launch of a phase takes the grid of grid_levels (>= levels), so that all
 // write the same partial rows.
@@ -160,8 +165,12 @@ constexpr int kFusedMinLines = 16;    // fewest lines of a wave (each walks 2*le
 // More levels move fewer bytes per step but walk more lines and lanes twice;
 // the column sums (16 registers a level) drop the waves per SIMD from 4 to 3
 // above 3 levels in FP32, 4 in FP64.
+// ACC_NORM, whole adaptive estimates in ms: FP32, 2048^2, 32 queries of about 49
+// steps 14.2 with 3 levels, 11.7 with 4, 11.0 with 5 (30.0 one step at a time);
+// 1024^2, 16 queries of 2 to 11 steps 1.30 with 4, 1.43 with 5, 1.46 with 6: 4,
+// since columns stop inside a launch and more levels repeat more.
 constexpr int fused_levels(int kind, bool f64) {
-    return kind == STEP_HORNER_SIGNS ? 6 : kind == STEP_HORNER_VEC ? 4 : f64 ? 4 : 3;
+    return kind == STEP_HORNER_SIGNS ? 6 : kind == STEP_HORNER_VEC || kind == STEP_ACC_NORM ? 4 : f64 ? 4 : 3;
 }
 struct FusedArgs {
     int kind, levels, grid_levels;
@@ -185,6 +194,10 @@ struct FusedArgs {
     int part_ld;
     int max_parts;                    // most partial rows (0: no limit)
     int nt_out;
+    const void* pin;
+    void* pout;
+    const uint64_t* active;
+    const int* run;
     double init_scale;
     double mid[kFusedMax], nbeta[kFusedMax], dj[kFusedMax];   // off[2] - beta, -beta
 };
@@ -246,11 +259,11 @@ hipError_t launch_gauss_fill(bool f64, int n, int k, uint64_t key, int col0, dou
 hipError_t launch_scale_copy(bool f64, int n, int ncols, const void* V, int ldv, double scale,
                              void* out, int ldo, hipStream_t st);
 
-// Row-major V (n x ncols, leading dimension ncols, any alignment) to and from
+// Row-major V (n x ncols, leading dimension ldv, any alignment) to and from
 // 16-byte column chunks one after another (chunk q: n x VEC; columns past ncols
 // are zero).
-hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, void* chunks, hipStream_t st);
-hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, hipStream_t st);
+hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, int ldv, void* chunks, hipStream_t st);
+hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, int ldv, hipStream_t st);
 
 // Partial cross products X^T Z per workgroup, FP64: part[wg][i*kz+j],
 // cross_num_wg(n) rows.  Z is a second block, or, with zmask (one word per
@@ -385,6 +398,21 @@ hipError_t launch_dia_build(bool f64, const CsrDev& A, void* dia, uint16_t* pres
 // the caller).  One wave; sums are FP64 column sums of w_m^2.
 hipError_t launch_adapt_decide(const double* sums, int stride, int qc, double dm_abs, double tol, int m,
                                uint64_t* mask, int* deg, hipStream_t st);
+
+// The same test after `levels` steps taken together: level t = 0..levels-1
+// produced w_{m+1+t}, sums[t*stride_t + c].  words (device): [0] the mask, in
+// and out; [1 + t] the columns active before level t; [kAdaptNext + t] the new
+// mask, for every t; [kAdaptRan] counts the calls that found an active column.
+// *redo = 1 if some column stopped before the last level (it took terms that it
+// should not have).  levels = 0 starts a loop: fills [kAdaptNext ..], clears
+// [kAdaptRan].
+constexpr int kAdaptNext = 7, kAdaptRan = 15, kAdaptWords = 16;
+static_assert(kAdaptNext + kFusedMax <= kAdaptRan, "words of the levels");
+struct AdaptLevels {
+    double dm_abs[kFusedMax];
+};
+hipError_t launch_adapt_decide_levels(const double* sums, int stride_t, int qc, const AdaptLevels& lv, int levels,
+                                      double tol, int m, uint64_t* words, int* redo, int* deg, hipStream_t st);
 
 // Lanczos recurrence (lanczos.hip): step j of the FP64 recurrence on A, u = u_j,
 // u_prev = u_{j-1}, w becomes u_{j+1} (all unnormalised); alpha[j], and beta of

@@ -1302,11 +1302,12 @@ hipError_t launch_scale_copy(bool f64, int n, int ncols, const void* V, int ldv,
 // Row-major <-> column chunks: a wave takes 64 rows of one chunk, a workgroup
 // four chunks of the same rows (their pieces of a row share cache lines).
 template <typename T, bool PACK>
-__global__ __launch_bounds__(kThreads) void chunk_copy_kernel(int n, int ncols, T* __restrict__ V, T* __restrict__ chunks) {
+__global__ __launch_bounds__(kThreads) void chunk_copy_kernel(int n, int ncols, T* __restrict__ V, int ldv,
+                                                              T* __restrict__ chunks) {
     constexpr int V16 = 16 / (int)sizeof(T);
     const int r = blockIdx.x * 64 + (threadIdx.x & 63), q = blockIdx.y * kWaves + (threadIdx.x >> 6);
     if (r >= n || q * V16 >= ncols) return;
-    T* const row = V + (size_t)r * ncols + q * V16;
+    T* const row = V + (size_t)r * ldv + q * V16;
     T* const at = chunks + ((size_t)q * n + r) * V16;
     const int have = min(V16, ncols - q * V16);
     Pack<T, V16> p;
@@ -1323,25 +1324,25 @@ __global__ __launch_bounds__(kThreads) void chunk_copy_kernel(int n, int ncols, 
 }
 
 template <bool PACK>
-hipError_t launch_chunk_copy(bool f64, int n, int ncols, void* V, void* chunks, hipStream_t st) {
+hipError_t launch_chunk_copy(bool f64, int n, int ncols, void* V, int ldv, void* chunks, hipStream_t st) {
     if (n == 0 || ncols == 0) return hipSuccess;
     const int nq = div_up(ncols, f64 ? 2 : 4);
     const dim3 grid(div_up(n, 64), div_up(nq, kWaves));
     if (grid.y > 65535) return hipErrorInvalidValue;
     if (f64)
         hipLaunchKernelGGL((chunk_copy_kernel<double, PACK>), grid, dim3(kThreads), 0, st, n, ncols, (double*)V,
-                           (double*)chunks);
+                           ldv, (double*)chunks);
     else
         hipLaunchKernelGGL((chunk_copy_kernel<float, PACK>), grid, dim3(kThreads), 0, st, n, ncols, (float*)V,
-                           (float*)chunks);
+                           ldv, (float*)chunks);
     return hipGetLastError();
 }
 
-hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, void* chunks, hipStream_t st) {
-    return launch_chunk_copy<true>(f64, n, ncols, const_cast<void*>(V), chunks, st);
+hipError_t launch_pack_chunks(bool f64, int n, int ncols, const void* V, int ldv, void* chunks, hipStream_t st) {
+    return launch_chunk_copy<true>(f64, n, ncols, const_cast<void*>(V), ldv, chunks, st);
 }
-hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, hipStream_t st) {
-    return launch_chunk_copy<false>(f64, n, ncols, V, const_cast<void*>(chunks), st);
+hipError_t launch_unpack_chunks(bool f64, int n, int ncols, const void* chunks, void* V, int ldv, hipStream_t st) {
+    return launch_chunk_copy<false>(f64, n, ncols, V, ldv, const_cast<void*>(chunks), st);
 }
 
 // ---------------------------------------------------------------------------
@@ -2387,6 +2388,41 @@ __global__ __launch_bounds__(64) void adapt_decide_kernel(const double* __restri
     }
     const uint64_t now = __ballot(keep);
     if (c == 0) *mask = now;
+}
+
+__global__ __launch_bounds__(64) void adapt_levels_kernel(const double* __restrict__ sums, int stride_t, int qc,
+                                                          AdaptLevels lv, int levels, double tol, int m,
+                                                          uint64_t* __restrict__ words, int* __restrict__ redo,
+                                                          int* __restrict__ deg) {
+    const int c = threadIdx.x;
+    const uint64_t start = words[0];
+    uint64_t mask = start;
+    int again = 0;
+    for (int t = 0; t < levels; ++t) {
+        if (c == 0) words[1 + t] = mask;
+        again |= mask != start;
+        bool keep = false;
+        if (c < qc && ((mask >> c) & 1ull)) {
+            const double e = lv.dm_abs[t] * sqrt(fmax(sums[(size_t)t * stride_t + c], 0.0));
+            keep = e > tol;
+            if (!keep) deg[c] = m + 1 + t;
+        }
+        mask = __ballot(keep);
+    }
+    if (c < kFusedMax) words[kAdaptNext + c] = mask;
+    if (c == 0) {
+        words[0] = mask;
+        words[kAdaptRan] = levels == 0 ? 0 : words[kAdaptRan] + (start != 0);
+        *redo = again;
+    }
+}
+
+hipError_t launch_adapt_decide_levels(const double* sums, int stride_t, int qc, const AdaptLevels& lv, int levels,
+                                      double tol, int m, uint64_t* words, int* redo, int* deg, hipStream_t st) {
+    if (qc < 1 || qc > 64 || levels < 0 || levels > kFusedMax) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(adapt_levels_kernel, dim3(1), dim3(64), 0, st, sums, stride_t, qc, lv, levels, tol, m, words,
+                       redo, deg);
+    return hipGetLastError();
 }
 
 hipError_t launch_adapt_decide(const double* sums, int stride, int qc, double dm_abs, double tol, int m,
