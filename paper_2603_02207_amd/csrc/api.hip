@@ -2094,9 +2094,8 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
             LD_CHECK(run_step(f64, A, s, qc, qc, st, &nwg, lr));
             if (nwg > nwg_max) return fail(LD_EINVAL, "internal: partial sums overflow");
             if (launches) *launches += 1;
-            LD_CHECK_HIP(launch_reduce(b.part, nwg, qc, 64, 1, 0, b.sums, qc, st));
-            LD_CHECK_HIP(
-                launch_adapt_decide(b.sums, 1, qc, std::fabs(p.d[j + 1]), tol, j + 1, b.mask, b.deg + q0, st));
+            LD_CHECK_HIP(launch_reduce_decide(b.part, nwg, qc, 64, std::fabs(p.d[j + 1]), tol, j + 1, b.mask,
+                                              b.deg + q0, st));
             cur = out;
             const int done = j + 1;   // poll after steps 1, 2, 4, then every kAdaptPoll: stop once all columns are done
             if (done < m && (done == 1 || done == 2 || done == 4 || done % kAdaptPoll == 0)) {

@@ -399,6 +399,10 @@ hipError_t launch_dia_build(bool f64, const CsrDev& A, void* dia, uint16_t* pres
 hipError_t launch_adapt_decide(const double* sums, int stride, int qc, double dm_abs, double tol, int m,
                                uint64_t* mask, int* deg, hipStream_t st);
 
+// The column sums of a step's partials (nwg rows) and that test, in one launch.
+hipError_t launch_reduce_decide(const double* part, int nwg, int qc, int part_ld, double dm_abs, double tol, int m,
+                                uint64_t* mask, int* deg, hipStream_t st);
+
 // The same test after `levels` steps taken together: level t = 0..levels-1
 // produced w_{m+1+t}, sums[t*stride_t + c].  words (device): [0] the mask, in
 // and out; [1 + t] the columns active before level t; [kAdaptNext + t] the new
