@@ -275,12 +275,28 @@ KERNEL_PREFIXES = {
     ("sketch_horner", "step_kernel"): ("step_kernel<float, 4, 0, false",),
     ("sketch_horner", "dia_flat_kernel"): ("dia_flat_kernel<float, 4, 0,",),
     ("quadform", "step_kernel"): ("step_kernel<float, 4, 3, false", "step_kernel<float, 4, 2, false"),
+    # several steps per launch; the template arguments after the step kind are the levels and the first-launch flag
+    ("sketch_horner", "fused_kernel"): ("fused_kernel<float, 4, 0, 6, false",),
+    ("quadform", "fused_kernel"): ("fused_kernel<float, 4, 3, 3, false",),
 }
 
 
+def steps_per_launch(tag: str, st) -> float:
+    """Newton steps of a phase over its launches (1 when the degree is not recorded)."""
+    if "degree" not in st:
+        return 1.0
+    if tag == "sketch_horner":
+        return -(-st["k"] // st["block_cols1"]) * st["degree"] / st["launches1"]
+    steps = st["degree"] if st["dot_mode_used"] == 1 else -(-st["degree"] // 2)
+    return -(-(st["k"] + st["k_G"]) // st["block_cols23"]) * steps / st["launches23"]
+
+
 def step_kernel_name(tag: str, st) -> str:
-    """Kernel of a phase's Newton steps: on diagonal storage the sketch's
+    """Kernel of a phase's Newton steps: one launch for several of them on
+    constant five-point stencils; on other diagonal storage the sketch's
     steps (no column sums) take the one-chunk-per-thread kernel."""
+    if steps_per_launch(tag, st) > 1:
+        return "fused_kernel"
     return "dia_flat_kernel" if tag == "sketch_horner" and st.get("dia_diagonals") else "step_kernel"
 
 
@@ -502,11 +518,18 @@ def kernel_records(st):
         if nl:
             avg_s = ms / 1e3 / nl
             kernels[tag] = {"kernel": step_kernel_name(tag, st), "launches": nl, "avg_us": avg_s * 1e6,
-                            "bytes_per_launch": by / nl,
+                            "bytes_per_launch": by / nl, "steps_per_launch": steps_per_launch(tag, st),
                             "GBps": by / nl / avg_s / 1e9, "total_ms": ms,
                             # kernel dispatches per library launch (row ranges of a streaming step)
                             "dispatches_per_launch": st.get("ranges23", 1) if tag == "quadform" else 1}
     return kernels
+
+
+def step_bound(rec) -> str:
+    """What bounds a phase's launches: several steps in one are bound by the vector ALUs (the block moves once)."""
+    if rec["kernel"] == "fused_kernel":
+        return "valu"
+    return "infinity_cache" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
 
 
 def run_workload(args, workload, steps):
@@ -559,7 +582,7 @@ def run_workload(args, workload, steps):
     value = args.steps / dt
 
     # dominant recurrence kernel, timed by HIP events on the launch stream
-    kernels = kernel_records(st)
+    kernels = kernel_records({**st, "degree": cfg["degree"]})
     dom = max(kernels, key=lambda k: kernels[k]["total_ms"])
     achieved = kernels[dom]["GBps"]
     traffic = (measured_traffic(dom, args.workload, kernels[dom]["kernel"])
@@ -607,7 +630,7 @@ def run_workload(args, workload, steps):
             "parallelism": "single GPU",
         },
         "roofline": {
-            "bound": "infinity_cache" if in_cache else "hbm",
+            "bound": step_bound(kernels[dom]),
             "kernel": f"{kernels[dom]['kernel']} ({dom})",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
@@ -724,7 +747,7 @@ def run_workload(args, workload, steps):
                            csr_only=1)
         k_c = max(3, args.steps // 2)
         e_c, st_c, dt_c = time_estimates(ld, A32, lmin, lmax, degree, m_vec, args.seed, o_csr, k_c, 1)
-        kc = kernel_records(st_c)
+        kc = kernel_records({**st_c, "degree": degree})
         out["csr_only"] = {"value": k_c / dt_c, "ms_per_step": dt_c / k_c * 1e3, "estimate": e_c,
                            "matrix_storage": "csr" if not st_c["dia_diagonals"] else "diagonal",
                            "kernels": kc,
@@ -758,7 +781,7 @@ def large_record(args, name):
     lmin, lmax = ld.spectral_bounds(A)
     opts = ld.Options(trusted_csr=1)
     est, st, dt = time_estimates(ld, A, lmin, lmax, cfg["degree"], cfg["m_vec"], args.seed, opts, 5, 1)
-    kernels = kernel_records(st)
+    kernels = kernel_records({**st, "degree": cfg["degree"]})
     dom = max(kernels, key=lambda k: kernels[k]["total_ms"])
     for tag, rec in kernels.items():
         t = measured_traffic(tag, name, rec["kernel"])
@@ -779,7 +802,7 @@ def large_record(args, name):
                            if st.get("dia_diagonals") else "csr"),
         "column_blocks": {"sketch": st["block_cols1"], "quadform": st["block_cols23"]},
         "dominant_kernel": f"{kernels[dom]['kernel']} ({dom})",
-        "bound": "infinity_cache" if kernels[dom]["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm",
+        "bound": step_bound(kernels[dom]),
         "avg_us": kernels[dom]["avg_us"],
         "alg_bytes_per_launch": kernels[dom]["bytes_per_launch"],
         "achieved_GBps": kernels[dom]["GBps"],

@@ -69,3 +69,29 @@ def test_fused_adaptive_estimate():
         np.testing.assert_array_equal(deg, odeg)
         assert abs(est - one) <= 1e-11 * abs(one)
         assert st["launches1"] < st1["launches1"] and st["launches23"] < st1["launches23"]
+
+
+def test_fused_adaptive_smaller_workspace():
+    # a workspace without the four blocks of chunks takes one launch per step; one that is shorter still is refused
+    import ctypes
+    from paper_2603_02207_amd import _native as nat
+    csr = stencil(160, 50, 3, 20)
+    n, cols = csr[3], 17
+    A = ld.CSR.from_arrays(csr[0], csr[1], np.asarray(csr[2]), n, dtype=torch.float64)
+    V = torch.tensor(np.random.default_rng(3).standard_normal((n, cols)), device="cuda")
+    want, wdeg = ld.apply_log_adaptive(A, 0.25, 8.4, 60, 1e-3, V)
+    c, b = A.c_struct(), ctypes.c_size_t(0)
+    nat.check(nat.load().ld_workspace_size(ctypes.byref(c), 60, -cols, 1, None, ctypes.byref(b)), "size")
+    plain = b.value - 4 * ((n * 18 * 8 + 255) // 256 * 256)
+    for size, refused in ((plain, False), (plain - 256, True)):
+        ws = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        at = (ws.data_ptr() + 255) // 256 * 256
+        out, deg = torch.empty_like(V), np.zeros(cols, dtype=np.int32)
+        rc = nat.load().ld_apply_log_adaptive(
+            ctypes.byref(c), 0.25, 8.4, 60, 1e-3, ctypes.c_void_p(V.data_ptr()), ctypes.c_void_p(out.data_ptr()), cols,
+            None, ctypes.c_void_p(at), size, None, deg.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
+        assert rc == (nat.LD_EWORKSPACE if refused else nat.LD_OK)
+        if rc == nat.LD_OK:
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(deg, wdeg)
+            assert_cols_close(out.cpu().numpy(), want.cpu().numpy(), 1e-11)
