@@ -526,9 +526,10 @@ def kernel_records(st):
 
 
 def step_bound(rec) -> str:
-    """What bounds a phase's launches: several steps in one are bound by the vector ALUs (the block moves once)."""
+    """What bounds a phase's launches: several steps in one are bound by the vector ALUs (the block moves once
+    per launch), beyond the Infinity Cache by both."""
     if rec["kernel"] == "fused_kernel":
-        return "valu"
+        return "valu" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "valu and hbm"
     return "infinity_cache" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
 
 
