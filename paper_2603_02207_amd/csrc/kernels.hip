@@ -1304,26 +1304,29 @@ hipError_t launch_scale_copy(bool f64, int n, int ncols, const void* V, int ldv,
 }
 
 // Row-major <-> column chunks: a wave takes 64 rows of one chunk, a workgroup
-// four chunks of the same rows (their pieces of a row share cache lines).
+// four chunks of the same rows (their pieces of a row share cache lines), and
+// the next four beyond the grid's 65535 in y (2^20 columns are allowed).
 template <typename T, bool PACK>
 __global__ __launch_bounds__(kThreads) void chunk_copy_kernel(int n, int ncols, T* __restrict__ V, int ldv,
                                                               T* __restrict__ chunks) {
     constexpr int V16 = 16 / (int)sizeof(T);
-    const int r = blockIdx.x * 64 + (threadIdx.x & 63), q = blockIdx.y * kWaves + (threadIdx.x >> 6);
-    if (r >= n || q * V16 >= ncols) return;
-    T* const row = V + (size_t)r * ldv + q * V16;
-    T* const at = chunks + ((size_t)q * n + r) * V16;
-    const int have = min(V16, ncols - q * V16);
-    Pack<T, V16> p;
-    if constexpr (PACK) {
+    const int r = blockIdx.x * 64 + (threadIdx.x & 63);
+    if (r >= n) return;
+    for (int q = blockIdx.y * kWaves + (threadIdx.x >> 6); q * V16 < ncols; q += gridDim.y * kWaves) {
+        T* const row = V + (size_t)r * ldv + q * V16;
+        T* const at = chunks + ((size_t)q * n + r) * V16;
+        const int have = min(V16, ncols - q * V16);
+        Pack<T, V16> p;
+        if constexpr (PACK) {
 #pragma unroll
-        for (int e = 0; e < V16; ++e) p.v[e] = e < have ? row[e] : T(0);
-        store_pack<T, V16>(at, p);
-    } else {
-        p = load_pack<T, V16>(at);
+            for (int e = 0; e < V16; ++e) p.v[e] = e < have ? row[e] : T(0);
+            store_pack<T, V16>(at, p);
+        } else {
+            p = load_pack<T, V16>(at);
 #pragma unroll
-        for (int e = 0; e < V16; ++e)
-            if (e < have) row[e] = p.v[e];
+            for (int e = 0; e < V16; ++e)
+                if (e < have) row[e] = p.v[e];
+        }
     }
 }
 
@@ -1331,8 +1334,7 @@ template <bool PACK>
 hipError_t launch_chunk_copy(bool f64, int n, int ncols, void* V, int ldv, void* chunks, hipStream_t st) {
     if (n == 0 || ncols == 0) return hipSuccess;
     const int nq = div_up(ncols, f64 ? 2 : 4);
-    const dim3 grid(div_up(n, 64), div_up(nq, kWaves));
-    if (grid.y > 65535) return hipErrorInvalidValue;
+    const dim3 grid(div_up(n, 64), std::min(div_up(nq, kWaves), 65535));
     if (f64)
         hipLaunchKernelGGL((chunk_copy_kernel<double, PACK>), grid, dim3(kThreads), 0, st, n, ncols, (double*)V,
                            ldv, (double*)chunks);
