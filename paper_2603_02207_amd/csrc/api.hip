@@ -625,7 +625,7 @@ int fused_horner(const ld_csr* A, const FusedPlan& q, FusedArgs f, double add, c
 // one launch per step.
 bool resident_fits(const ld_csr* A, const LongRows& lr, const ld_options& o, int steps) {
     return lr.tile_order == LD_TILES_AUTO && o.block_cols <= 0 && !lr.list && A->nnz > 0 && steps <= kResidentSteps &&
-           A->n <= 8 * 1024 &&
+           A->n <= kResidentRows &&
            resident_lds(A->n, A->nnz, A->dtype == LD_F64 ? 8 : 4) <= (size_t)kResidentLds;
 }
 

@@ -218,6 +218,7 @@ hipError_t launch_fused(bool f64, const FusedArgs& f, hipStream_t st);
 //                  d[m]*w_m, each column to the first m with |d[m]| ||w_m|| <= tol
 //                  (deg[c] = m) or `steps`
 constexpr int kResidentSteps = 200;
+constexpr int kResidentRows = 4096;       // four of each of a workgroup's 1024 threads
 constexpr int kResidentParts = 16;
 constexpr int kResidentLds = 156 << 10;   // of a CU's 160 KB
 struct ResidentArgs {

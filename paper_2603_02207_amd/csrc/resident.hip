@@ -8,7 +8,14 @@
 // or V in registers.  Rows are summed in CSR order, products as in the
 // single-step kernels.  Measured on gfx950, 32^2 grid, FP32: 40 sketch steps over
 // 10 columns 220 -> 55 us, 20 quadratic-form steps over 20 columns 160 -> 75 us
-// (launches and gaps against one launch), the estimate 553 -> 358 us.
+// (launches and gaps against one launch), the estimate 553 -> 358 us.  Larger
+// matrices gain less, since one workgroup walks all rows of a chunk, and never
+// lose: FP32 estimates of degree 40 and 60 queries against single steps, 40^2
+// grid 559 -> 453 us, 50^2 556 -> 500, 58^2 559 -> 545; tridiagonal, 2500 rows
+// 533 -> 437, 4090 rows 542 -> 485.
+// More than four rows a thread do not fit its 128 registers: the column sums
+// spill from the fifth row, all kinds at eight, to scratch that the runtime may
+// have to allocate; such matrices keep single steps.
 //
 // Bound by LDS latency (a row's gathers) and the barriers.
 #include <hip/hip_runtime.h>
@@ -293,8 +300,7 @@ hipError_t launch_resident_k(const CsrDev& A, const ResidentDev<T>& d, hipStream
     }
     if (rpt <= 1) LD_RES(1)
     if (rpt <= 2) LD_RES(2)
-    if (rpt <= 4) LD_RES(4)
-    if (rpt <= 8) LD_RES(8)
+    if (rpt <= 4) LD_RES(4)   // kResidentRows
 #undef LD_RES
     return hipErrorInvalidValue;
 }
@@ -343,7 +349,7 @@ hipError_t launch_resident_t(const CsrDev& A, const ResidentArgs& f, hipStream_t
 size_t resident_lds(long long n, long long nnz, int elem) { return (size_t)(n * 16 + nnz * (elem + 2) + 15) / 16 * 16; }
 
 hipError_t launch_resident(bool f64, const CsrDev& A, const ResidentArgs& f, hipStream_t st) {
-    if (A.n < 1 || A.n > 65535 || f.steps < 1 || f.steps > kResidentSteps || f.cols < 1 ||
+    if (A.n < 1 || A.n > kResidentRows || f.steps < 1 || f.steps > kResidentSteps || f.cols < 1 ||
         resident_lds(A.n, A.nnz, f64 ? 8 : 4) > (size_t)kResidentLds)
         return hipErrorInvalidValue;
     return f64 ? launch_resident_t<double>(A, f, st) : launch_resident_t<float>(A, f, st);
