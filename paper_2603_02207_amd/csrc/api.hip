@@ -990,7 +990,7 @@ int estimate_dots(const ld_csr* A, EstimateState& S, hipStream_t st, std::vector
         if (D) {
             f = fused_args(A, S.longrows, S.fused, STEP_DOT_SQ, (m + 1) / 2, cols, D);
             f.max_parts = L.nwg_dot;
-            grid = fused_grid(n, D, cols, (int)L.elem, f.grid_levels, f.max_parts);
+            grid = fused_grid(STEP_DOT_SQ, n, D, cols, (int)L.elem, f.grid_levels, f.max_parts);
         }
         if (S.resident && !keep && S.mode == LD_DOT_SQUARED) {
             ResidentArgs f{};
@@ -1666,7 +1666,7 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
         if (S.fused_D) {
             // every block's quadratic forms or none: their coefficients are shared
             const FusedArgs f = fused_args(A, S.longrows, S.fused, STEP_DOT_SQ, (degree + 1) / 2, S.L.X.bw, S.fused_D);
-            if (fused_grid((int)A->n, S.fused_D, S.L.X.bw, (int)S.L.elem, f.grid_levels, S.L.nwg_dot).parts > S.L.nwg_dot)
+            if (fused_grid(STEP_DOT_SQ, (int)A->n, S.fused_D, S.L.X.bw, (int)S.L.elem, f.grid_levels, S.L.nwg_dot).parts > S.L.nwg_dot)
                 S.fused_D = 0;
             else
                 S.fused = fused_plan(A, S.longrows, S.plan);
@@ -1937,7 +1937,7 @@ FusedArgs adaptive_args(const ld_csr* A, const FusedPlan& q, int qc, int D, cons
 bool adaptive_fits(const ld_csr* A, const FusedPlan& q, int qc, int D, const AdaptBufs& b, const LongRows& lr) {
     const FusedArgs f = adaptive_args(A, q, qc, D, b, lr);
     return f.max_parts > 0 &&
-           fused_grid(f.n, D, qc, A->dtype == LD_F64 ? 8 : 4, f.grid_levels, f.max_parts).parts <= f.max_parts;
+           fused_grid(STEP_ACC_NORM, f.n, D, qc, A->dtype == LD_F64 ? 8 : 4, f.grid_levels, f.max_parts).parts <= f.max_parts;
 }
 
 // Alg. 2's loop on up to 64 columns of a five-point stencil, several steps per
@@ -1959,7 +1959,7 @@ int adaptive_fused(const ld_csr* A, const FusedPlan& q, double tol, double shift
     uint64_t* const words = b.mask;
     int* const redo = (int*)(words + kAdaptWords);
     FusedArgs f = adaptive_args(A, q, qc, D, b, lr);
-    const int parts = fused_grid(n, D, qc, elem, f.grid_levels, f.max_parts).parts;
+    const int parts = fused_grid(STEP_ACC_NORM, n, D, qc, elem, f.grid_levels, f.max_parts).parts;
     f.slot_stride = (long long)parts * f.part_ld;
     FusedBlock in = FusedBlock::rows(const_cast<void*>(V), ld, elem);
     if (ld % v != 0 || (uintptr_t)V % 16 != 0) {   // the second launch is the first to write chunks[1]

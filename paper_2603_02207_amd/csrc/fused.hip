@@ -348,7 +348,7 @@ hipError_t launch_fused_t(const FusedArgs& f, hipStream_t st) {
     d.n = f.n;
     d.D = f.D;
     d.lines = (int)(((long long)f.n + f.D - 1) / f.D);
-    const FusedGrid gr = fused_grid(f.n, f.D, f.bcols, (int)sizeof(T), f.grid_levels, f.max_parts);
+    const FusedGrid gr = fused_grid(f.kind, f.n, f.D, f.bcols, (int)sizeof(T), f.grid_levels, f.max_parts);
     d.rows_per_chunk = gr.rows;
     d.strips = gr.strips;
     d.width = 64 - 2 * f.grid_levels;
@@ -396,14 +396,16 @@ hipError_t launch_fused_t(const FusedArgs& f, hipStream_t st) {
 
 }  // namespace
 
-FusedGrid fused_grid(int n, int D, int bcols, int elem, int levels, int max_parts) {
+FusedGrid fused_grid(int kind, int n, int D, int bcols, int elem, int levels, int max_parts) {
     const int vec = 16 / elem, nq = (bcols + vec - 1) / vec;
     const int lines = (int)(((long long)n + D - 1) / D), width = 64 - 2 * levels;
     FusedGrid g{};
     g.strips = (D + width - 1) / width;
     int want = std::max(1, kFusedWaves / (g.strips * nq));   // line chunks that fill the device
     if (max_parts > 0) want = std::min(want, std::max(1, max_parts / g.strips));
-    g.rows = std::max((lines + want - 1) / want, std::min(lines, kFusedMinLines));
+    const int idle = std::max(1, fused_idle_waves(kind) / (g.strips * nq));
+    g.rows = std::max((lines + want - 1) / want,
+                      std::min({lines, kFusedMinLines, std::max(2, (lines + idle - 1) / idle)}));
     g.parts = g.strips * ((lines + g.rows - 1) / g.rows);
     return g;
 }

@@ -151,7 +151,8 @@ hipError_t launch_step(bool f64, const CsrDev& A, const StepArgs& s, hipStream_t
 constexpr int kFusedMax = 6;          // most levels of one launch
 constexpr int kFusedMinWidth = 128;   // shortest lines taken
 constexpr int kFusedWaves = 4096;     // waves a launch aims at: 4 per SIMD
-constexpr int kFusedMinLines = 16;    // fewest lines of a wave (each walks 2*levels more)
+constexpr int kFusedMinLines = 16;    // fewest lines of a wave (each walks 2*levels more), unless
+                                      // so many leave most of the device idle (fused_idle_waves)
 
 // Levels of one launch.  Measured on gfx950, us per step (1024^2 points; 20
 // FP32 / 10 FP64 columns), against the single-step kernels:
@@ -172,6 +173,16 @@ constexpr int kFusedMinLines = 16;    // fewest lines of a wave (each walks 2*le
 constexpr int fused_levels(int kind, bool f64) {
     return kind == STEP_HORNER_SIGNS ? 6 : kind == STEP_HORNER_VEC || kind == STEP_ACC_NORM ? 4 : f64 ? 4 : 3;
 }
+// Waves below which a wave takes fewer than kFusedMinLines lines, down to two: the
+// device is then mostly idle, a launch lasts as long as one wave's walk, and the
+// lines walked twice cost nothing.  Measured (us per step; 16, 8, 4, 2 lines, single
+// steps): sketch of 10 FP32 columns, 128 x 62 points 4.57, 3.10, 2.37, 1.95, 3.44;
+// quadratic forms of 20 columns 7.27, 5.38, 4.52, 3.92, 5.86; log(A) V, 60 steps,
+// one column, 150^2 350, 259, 220, 196, 316 us.  Near a full device two lines cost
+// more than eight (350^2, quadratic forms of 40 FP32 columns: 9.1, 8.6 at 4 to 8).
+// The adaptive launches' sums are reduced after every one of them, so more waves
+// cost more there (20000 x 8 points, one column: 569 us at 8 lines, 618 at two).
+constexpr int fused_idle_waves(int kind) { return kind == STEP_ACC_NORM ? 1024 : 2048; }
 struct FusedArgs {
     int kind, levels, grid_levels;
     bool init;
@@ -204,7 +215,7 @@ struct FusedArgs {
 struct FusedGrid {
     int strips, rows, parts;          // strips of a line, lines of a wave, partial rows
 };
-FusedGrid fused_grid(int n, int D, int bcols, int elem, int levels, int max_parts);
+FusedGrid fused_grid(int kind, int n, int D, int bcols, int elem, int levels, int max_parts);
 hipError_t launch_fused(bool f64, const FusedArgs& f, hipStream_t st);
 
 // Whole recurrences of a matrix whose CSR arrays and one 16-byte column chunk fit
