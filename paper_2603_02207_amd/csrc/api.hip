@@ -426,6 +426,9 @@ struct LongRows {
     int tile_order = LD_TILES_AUTO;   // ld_options.tile_order
     bool skewed = false;              // entries far from even over the eight row bands
     bool scattered = false;           // most sampled entries lie far from the diagonal
+    bool interleaved() const {
+        return tile_order == LD_TILES_INTERLEAVED || (tile_order == LD_TILES_AUTO && skewed);
+    }
 };
 
 // Chunked XCD bands for stencils (diagonal storage) whose widest diagonal
@@ -464,7 +467,8 @@ int run_step(bool f64, const ld_csr* A, StepArgs s, int ncols, int col_block, hi
     // Cache, within 3% of interleaved from HBM), but give one XCD most of
     // the work when the entries crowd into a few bands (a power-law graph
     // with its hubs first: 1.5x slower); then the tiles are interleaved.
-    s.interleave = lr.tile_order == LD_TILES_INTERLEAVED || (lr.tile_order == LD_TILES_AUTO && lr.skewed);
+    s.interleave = lr.interleaved();
+    s.scattered = lr.scattered;
     // Once a launch streams from HBM (working set beyond the Infinity Cache),
     // the output goes out with streaming stores: L2 then keeps more of the
     // input rows that neighbouring tiles gather (measured on gfx950: -7% on a
@@ -2242,6 +2246,31 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     return LD_OK;
 }
 
+// Rows of V that are no whole number of 16-byte vectors (three columns or more:
+// fewer move less as they are) go through padded copies: the steps' vector
+// accesses outweigh the two copies from a few steps on.  Diagonal storage always
+// gains (us per step, as V is, padded: pentadiagonal, 500000 rows, 17 FP32 columns
+// 45.6, 24.7).  CSR rows, fewer lanes to a padded row, may lose the staging of
+// their entries that V's own rows have (step_staging): band of 8, 600000 rows, 7
+// FP64 columns (7 lanes, 4 padded) 57, 83; 100000 rows, 9 FP32 (9 lanes, 3) 10.4,
+// 15.5; 27-point grid 64^3, 13 FP64 (13 lanes, 7) 69, 88.  Such rows stay as they
+// are, but for one or two lanes (7 FP32 columns 41.9, 36.7 at 600000 rows), long
+// own rows (13 FP32 columns on 4 lanes, mesh of 300000 rows 52.7, 32.7; 17 on 5
+// from about 140000 rows on) and very few tiles, where slices make up for it.
+bool pads_rows(const ld_csr* A, const LongRows& lr, const ld_options& o, int nc, int degree) {
+    const int v = A->dtype == LD_F64 ? 2 : 4;
+    if (o.block_cols > 0 || nc < 3 || nc % v == 0 || degree < 4) return false;
+    if (lr.dia_nd > 0 || lr.interleaved()) return true;
+    int vown = v;
+    while (nc % vown) vown /= 2;
+    const int cols = std::min(nc, 64), own = (cols + vown - 1) / vown, pad = (cols + v - 1) / v;
+    const auto staging = [&](int lanes) { return step_staging(A->n, A->nnz, lanes); };
+    const int tiles = step_tiles((int)A->n, pad);
+    if (staging(own) > 0.95) return true;
+    if (pad >= 6) return staging(pad) <= 1.1;
+    return staging(pad) <= 0.9 || pad <= 2 || tiles < 256 || (own > 10 && (pad < 5 || tiles >= 1100));
+}
+
 // Workspace of ld_apply_log: two blocks as V is stored, or, packed, V and two
 // blocks with rows padded to whole 16-byte vectors (not asked for above
 // kPackMost bytes a block).
@@ -2356,10 +2385,7 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
         }
         if (!whole) LD_CHECK_HIP(launch_unpack_chunks(f64, n, nc, B0, PV, nc, st));
     } else {
-        // Rows of V that are no whole number of 16-byte vectors (three columns or
-        // more: fewer move less as they are) go through padded copies: the steps'
-        // vector accesses outweigh the two copies from a few steps on.
-        const bool pad = room && o.block_cols <= 0 && nc >= 3 && nc % v != 0 && m >= 4;
+        const bool pad = room && pads_rows(A, lr, o, nc, m);
         const int ld = pad ? ldp : nc;
         const void* src = V;
         if (pad) {

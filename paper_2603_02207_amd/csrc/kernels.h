@@ -91,6 +91,7 @@ struct StepArgs {
     // takes tiles w, w + grid, ... (spreads each tile's neighbours over the
     // XCDs; faster once the blocks stream from HBM)
     int interleave;
+    int scattered = 0;   // most entries lie far from the diagonal (CSR slices)
     // with interleave = 0: > 0 cuts the bands into chunks of about this many
     // rows, chunk c going to XCD c % 8 (each XCD walks its chunks in order);
     // 0 = one contiguous band per XCD
@@ -115,6 +116,11 @@ int step_max_cols(bool f64, const StepArgs& s);
 // 16-byte aligned blocks of at most bcols columns, and for any layout.
 int step_num_wg_bound(int n, int bcols, int elem_bytes);
 int step_num_wg_any(int n);
+// Entries of the rows a wave of the row-group CSR kernel takes in one pass, over
+// those it can stage in LDS (the row's columns on lpr lanes).
+double step_staging(long long n, long long nnz, int lpr);
+// Row tiles of a CSR launch with lpr lanes a row.
+int step_tiles(int n, int lpr);
 // Rows of one tile of the column-sum kinds over bcols columns of 16-byte aligned blocks.
 int step_tile_rows(int bcols, int elem_bytes);
 

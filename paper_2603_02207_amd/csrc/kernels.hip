@@ -861,6 +861,59 @@ int resident_wgs(const void* fn, int nt) {
     return r;
 }
 
+// Slices of a CSR row (csr_slice_kernel), 1 for the row groups of step_kernel.
+// Rows of more than kMaxDiag entries on average may go in slices; at most that
+// many (every matrix that the diagonal storage could hold among them) keep a row
+// group per row, whose sums are the diagonal storage's in its order.
+//
+// The line is what a wave of step_kernel stages: while its rows' entries fit
+// kWaveNz, their columns and values wait in LDS and the row groups are the
+// faster form at any size; beyond that each row group fetches them itself, a
+// batch after another, and slices, which need fewer batches, are.  Measured (us
+// per sketch step; 1, 2, 4 slices), rows of 17 entries in a band of 8:
+//   fits, 100000 rows, 24 FP32 columns (6 lanes) 11.9, 16.9, 26.3, 20 FP64
+//     (10 lanes) 20.0, 31.0, 55.9, 32 FP64 (16 lanes) 23.5, 42.8, 55.8
+//   does not, 16 FP32 columns (4 lanes) 13.2, 11.9, 14.7, 8 (2 lanes; 200000
+//     rows) 24.4, 15.4, 17.3, 4 (1 lane) 19.1, 13.5, 11.1
+// 27-point grid, 26 entries, 24 FP32 columns (fits not) 36.3, 24.5, 33.8 at 48^3,
+// 134, 93, 142 at 80^3; 20 FP64 (fits) 28.1, 42.5.  Rows of uneven length
+// overflow before their average does, which tells while the device is not full
+// (mesh of 15.5 entries, 5 lanes, 0.97 of the room: 36441 rows 12.5, 8.9; 100000
+// rows 19.6, 21.0): hence 0.95 below 600 tiles.  Below 200 tiles two slices bring
+// a tenth to eight lanes or fewer even so (10000 rows, 24 FP32 columns 6.3, 5.6).
+// Four slices: rows long enough, very few tiles, columns scattered over the rows
+// (each gather a miss: 2^18 rows of 17, 8 FP32 columns 57, 66, 57), and the one-
+// and three-lane rows as above (12 FP32 columns, 100000 rows 15.4, 13.1, 12.2).
+// With more than 10 lanes, slices that leave a tenth more of the wave idle lose
+// (24 FP64 columns, 61 entries, 106, 111).
+//
+// The kinds with column sums have workgroups that walk several tiles one after
+// another; there two slices pay only on narrow rows (quadratic forms, mesh of
+// 36441 rows, 8 FP64 columns 15.1, 9.4, 10.1; 20 11.7, 15.6, 19.5).  Where the
+// rows' lengths differ much (interleaved tiles), slices even out the waves in
+// both (power-law graph of 50000 rows, 32 FP64 columns: sketch 103, 76, quadratic
+// forms 106, 80).
+int csr_slices(bool sums, int lpr, int ntiles, const CsrDev& A, bool uneven, bool scattered) {
+    if ((long long)A.nnz <= (long long)kMaxDiag * A.n) return 1;
+    const double room = ntiles < 600 ? 0.95 : 1.0;
+    const bool fits = step_staging(A.n, A.nnz, lpr) <= room;
+    int slices;
+    if (uneven) {
+        slices = ntiles < 2048 ? (sums ? 2 : 4) : ntiles < 4096 ? 2 : 1;
+    } else if (sums) {
+        slices = fits || ntiles >= 2048 || lpr > 4 ? 1 : scattered && lpr <= 2 ? 4 : 2;
+    } else if (fits) {
+        slices = ntiles < 200 && lpr <= 8 ? 2 : 1;
+    } else {
+        const bool four = lpr == 1 || lpr == 3 || ntiles < 256 || (lpr <= 5 && (long long)A.nnz >= 24ll * A.n) ||
+                          (lpr <= 4 && scattered);
+        slices = ntiles < 2048 && four ? 4 : 2;
+        if (ntiles >= 1024 && 20 * (64 / (2 * lpr)) < 9 * (64 / lpr)) slices = 1;
+    }
+    while (slices > 1 && lpr * slices > 32) slices /= 2;
+    return slices;
+}
+
 template <typename T, int VEC, int KIND, bool FIRST>
 hipError_t launch_step_t(const CsrDev& A, const StepArgs& s, hipStream_t st, int* nwg_out) {
     constexpr int kIters = kStepIters;
@@ -1002,22 +1055,8 @@ hipError_t launch_step_t(const CsrDev& A, const StepArgs& s, hipStream_t st, int
                            s.long_count, part_row0, (T*)s.acc, s.ldacc, s.acc_cols, s.active);
         return hipGetLastError();
     };
-    // Rows of more than kMaxDiag entries on average go in slices; at most that
-    // many (every matrix that the diagonal storage could hold among them) keep a
-    // row group per row, whose sums are the diagonal storage's in its order.
-    // Slices pay while the row groups' own tiles are too few to fill the device,
-    // and for the kinds with column sums, whose workgroups walk several tiles one
-    // after another, only where a slice is narrow or the rows' lengths differ
-    // much.  Measured (us per step; 1, 2, 4, 8 slices), mesh of 15.5 entries a
-    // row: sketch, 36441 rows, 4 FP64 columns 12.2, 6.2, 5.8, 6.6, 20 FP32
-    // columns 12.5, 8.9, 8.8, 15.2; 400000 rows (3125 tiles), 8 FP64 columns
-    // 57.7, 46.7, 56.1, (4166 tiles) 20 FP32 columns 50.3, 59.3, 67.3; quadratic
-    // forms, 36441 rows, 8 FP64 columns 15.1, 9.4, 10.1, 11.0, 20 columns 11.7,
-    // 15.6, 19.5; power-law graph of 300000 rows, 20 FP32 columns 136, 122, 119.
-    int slices = ntiles < 2048 ? 4 : ntiles < 4096 ? 2 : 1;
-    if (is_dot(KIND)) slices = (ntiles < 2048 && lpr <= 4) || (ntiles < 4096 && s.interleave) ? 2 : 1;
-    while (slices > 1 && lpr * slices > 32) slices /= 2;
-    if ((long long)A.nnz > (long long)kMaxDiag * A.n && slices > 1) {
+    const int slices = csr_slices(is_dot(KIND), lpr, ntiles, A, s.interleave, s.scattered);
+    if (slices > 1) {
         const int rows = kWaves * (64 / (lpr * slices)), tiles = div_up(A.n, rows);
         // (the partial rows of the long-row launch too, where there is none)
         const int most = step_num_wg_bound(A.n, s.bcols, (int)sizeof(T)) - (skip ? kLongWgs : 0);
@@ -1094,6 +1133,12 @@ int step_num_wg_bound(int n, int bcols, int elem_bytes) {
 }
 
 int step_max_cols(bool f64, const StepArgs& s) { return 64 * pick_vec(s, f64 ? 8 : 4); }
+
+double step_staging(long long n, long long nnz, int lpr) {
+    return (double)kStepIters * (64 / lpr) * (double)nnz / ((double)n * kWaveNz);
+}
+
+int step_tiles(int n, int lpr) { return div_up(n, kWaves * (64 / lpr) * kStepIters); }
 
 int step_tile_rows(int bcols, int elem_bytes) {
     return (threads_of(STEP_DOT_SQ) / 64) * (64 / lanes_per_row(bcols, 16 / elem_bytes)) * kStepIters;
