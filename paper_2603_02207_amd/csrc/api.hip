@@ -1944,6 +1944,20 @@ bool adaptive_fits(const ld_csr* A, const FusedPlan& q, int qc, int D, const Ada
            fused_grid(STEP_ACC_NORM, f.n, D, qc, A->dtype == LD_F64 ? 8 : 4, f.grid_levels, f.max_parts).parts <= f.max_parts;
 }
 
+// Whether columns of norm at most `top` are expected to stop at step 1 or 2: a
+// launch of four steps, its repeat and the copies to and from chunks then cost
+// more than two steps (us, several steps per launch against one; 32 columns: FP32,
+// 1000^2 points, stop at step 1 687, 433, at 2 668, 566, at 3 673, 813; FP64 995,
+// 623, 993, 918, 994, 1478; 200^2 235, 180, 231, 215, 233, 267).  The norm of w_m is
+// |pi_m(T) v|, and pi_1 = x - 2 and pi_2 = x^2 - 4 are 2.2 and 3.2 in the mean over
+// a five-point stencil's spectrum.
+bool short_loop(const FusedPlan& q, double tol, double top) {
+    const int m = (int)q.mid.size();
+    for (int j = 1; j <= std::min(2, m); ++j)
+        if (3.0 * std::fabs(q.d[j]) * top <= tol) return true;
+    return m <= 2;
+}
+
 // Alg. 2's loop on up to 64 columns of a five-point stencil, several steps per
 // launch (from degree 0, whose test has set the mask; every result of P is
 // written here).  A launch takes its levels for every column that is active when
@@ -1954,7 +1968,8 @@ bool adaptive_fits(const ld_csr* A, const FusedPlan& q, int qc, int D, const Ada
 // mask after the first launch and then after every second one.
 // Measured (gfx950, FP32, 2048^2, 32 queries, about 49 steps): a launch of four
 // steps 290 us against 4 x (267 + 15) us one step at a time; the estimate 30.0 ->
-// 11.7 ms.  Short loops gain too (2..11 steps at 1024^2, 16 queries: 1.3 ms).
+// 11.7 ms.  Short loops gain too, from three steps on (2..11 steps at 1024^2, 16
+// queries: 1.3 ms; short_loop).
 int adaptive_fused(const ld_csr* A, const FusedPlan& q, double tol, double shift, const void* V, int ld, int qc,
                    void* P, int ldp, int D, const AdaptBufs& b, int* deg, const LongRows& lr, hipStream_t st,
                    int* launches) {
@@ -1971,7 +1986,6 @@ int adaptive_fused(const ld_csr* A, const FusedPlan& q, double tol, double shift
         in = FusedBlock::chunks(b.chunks[1], n, elem);
     }
     AdaptLevels lv{};
-    LD_CHECK_HIP(launch_adapt_decide_levels(b.sums, 0, qc, lv, 0, tol, 0, words, redo, deg, st));   // words[kAdaptNext..]
     int cur = 0, done = 0;
     uint64_t h[kAdaptWords] = {};
     for (int i = 0; done < m; ++i) {
@@ -2066,16 +2080,23 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
         LD_CHECK_HIP(hipMemcpyAsync(b.mask, &all, 8, hipMemcpyHostToDevice, st));
         LD_CHECK_HIP(launch_adapt_decide(b.sums, qc + 1, qc, std::fabs(p.d[0]), tol, 0, b.mask, b.deg + q0, st));
         {   // columns that stop at degree 0 need no product at all
-            uint64_t h = 0;
-            LD_CHECK_HIP(hipMemcpyAsync(&h, b.mask, 8, hipMemcpyDeviceToHost, st));
+            bool fuse = D && adaptive_fits(A, fp, qc, D, b, lr);
+            uint64_t h[kAdaptWords] = {};
+            if (fuse)   // starts adaptive_fused's words
+                LD_CHECK_HIP(launch_adapt_decide_levels(b.sums, qc + 1, qc, AdaptLevels{}, 0, tol, 0, b.mask,
+                                                        (int*)(b.mask + kAdaptWords), b.deg + q0, st));
+            LD_CHECK_HIP(hipMemcpyAsync(h, b.mask, fuse ? sizeof(h) : 8, hipMemcpyDeviceToHost, st));
             LD_CHECK_HIP(hipStreamSynchronize(st));
-            if (h != 0 && D && adaptive_fits(A, fp, qc, D, b, lr)) {
+            double top = 0.0;
+            std::memcpy(&top, &h[kAdaptTop], sizeof(top));
+            fuse = fuse && !short_loop(fp, tol, top);
+            if (h[0] != 0 && fuse) {
                 LD_CHECK(adaptive_fused(A, fp, tol, shift, Vq, ld, qc, Pq, ldp, D, b, b.deg + q0, lr, st, launches));
                 continue;
             }
             // P_0 = (d_0 + shift) w_0, w_0 = v
             LD_CHECK_HIP(launch_scale_copy(f64, n, qc, Vq, ld, p.d[0] + shift, Pq, ldp, st));
-            if (h == 0) continue;
+            if (h[0] == 0) continue;
         }
         const uint8_t* cur = Vq;
         for (int j = 0; j < m; ++j) {

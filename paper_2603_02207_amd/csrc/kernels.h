@@ -427,9 +427,10 @@ hipError_t launch_reduce_decide(const double* part, int nwg, int qc, int part_ld
 // mask, for every t; [kAdaptRan] counts the calls that found an active column.
 // *redo = 1 if some column stopped before the last level (it took terms that it
 // should not have).  levels = 0 starts a loop: fills [kAdaptNext ..], clears
-// [kAdaptRan].
-constexpr int kAdaptNext = 7, kAdaptRan = 15, kAdaptWords = 16;
-static_assert(kAdaptNext + kFusedMax <= kAdaptRan, "words of the levels");
+// [kAdaptRan]; sums[c * stride_t] is then the columns' own, and [kAdaptTop] their
+// largest norm (as a double) over the active ones.
+constexpr int kAdaptNext = 7, kAdaptTop = 14, kAdaptRan = 15, kAdaptWords = 16;
+static_assert(kAdaptNext + kFusedMax <= kAdaptTop, "words of the levels");
 struct AdaptLevels {
     double dm_abs[kFusedMax];
 };

@@ -2505,8 +2505,14 @@ __global__ __launch_bounds__(64) void adapt_levels_kernel(const double* __restri
         mask = __ballot(keep);
     }
     if (c < kFusedMax) words[kAdaptNext + c] = mask;
+    double norm = 0.0;
+    if (levels == 0) {
+        if (c < qc && ((mask >> c) & 1ull)) norm = sqrt(fmax(sums[(size_t)c * stride_t], 0.0));
+        for (int h = 32; h >= 1; h >>= 1) norm = fmax(norm, __shfl_xor(norm, h, 64));
+    }
     if (c == 0) {
         words[0] = mask;
+        if (levels == 0) words[kAdaptTop] = (uint64_t)__double_as_longlong(norm);
         words[kAdaptRan] = levels == 0 ? 0 : words[kAdaptRan] + (start != 0);
         *redo = again;
     }
