@@ -2032,14 +2032,24 @@ int adaptive_fused(const ld_csr* A, const FusedPlan& q, double tol, double shift
 // at.  Chunks of 64 columns; the host polls the active mask before the first
 // step, after steps 1, 2, 4 and then every kAdaptPoll steps, and stops a
 // chunk once no column is active.  `launches` counts the Newton steps.
+//
+// lost (nc entries, when asked for): what the quadratic form v^T P misses because
+// P_0 = d_0 v takes d_0 rounded to FP32, (d_0 - fl(d_0)) ||v||^2, for the loops of
+// several steps per launch.  There d_1 and the later coefficients belong to the
+// moved centres, and their roundings no longer cancel half of d_0's, as those of
+// the single steps do (sigma = lambda_min makes d_1 = d_0 / 4 there): the rounding
+// of d_0 is then most of the error of the estimate.  FP32, 130 x 60 and 300^2
+// points, rms over 16 matrices: 5.5e-8 one step per launch, 8.5e-8 several, 3.7e-8
+// with this.
 int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, const void* V, int ld, int nc,
                    void* P, int ldp, const AdaptBufs& b, const LongRows& lr, bool resident, hipStream_t st,
-                   std::vector<int>& hdeg, int* launches) {
+                   std::vector<int>& hdeg, int* launches, std::vector<double>* lost = nullptr) {
     const bool f64 = A->dtype == LD_F64;
     const size_t elem = f64 ? 8 : 4;
     const int n = (int)A->n;
     const int nwg_max = step_num_wg_any(n);
     const int m = p.degree;
+    if (lost) lost->assign((size_t)nc, 0.0);
     if (resident) {   // the whole loop in one launch, no polling
         ResidentArgs f{};
         f.kind = STEP_ACC_NORM;
@@ -2085,12 +2095,19 @@ int adaptive_apply(const ld_csr* A, const Plan& p, double tol, double shift, con
             if (fuse)   // starts adaptive_fused's words
                 LD_CHECK_HIP(launch_adapt_decide_levels(b.sums, qc + 1, qc, AdaptLevels{}, 0, tol, 0, b.mask,
                                                         (int*)(b.mask + kAdaptWords), b.deg + q0, st));
+            const double d0 = fp.d.empty() ? 0.0 : fp.d[0] + shift, rest = f64 ? 0.0 : d0 - (double)(float)d0;
+            std::vector<double> g;   // ||v||^2 on its diagonal
+            if (lost && fuse && rest != 0.0) {
+                g.resize((size_t)qc * qc);
+                LD_CHECK_HIP(hipMemcpyAsync(g.data(), b.sums, g.size() * 8, hipMemcpyDeviceToHost, st));
+            }
             LD_CHECK_HIP(hipMemcpyAsync(h, b.mask, fuse ? sizeof(h) : 8, hipMemcpyDeviceToHost, st));
             LD_CHECK_HIP(hipStreamSynchronize(st));
             double top = 0.0;
             std::memcpy(&top, &h[kAdaptTop], sizeof(top));
             fuse = fuse && !short_loop(fp, tol, top);
             if (h[0] != 0 && fuse) {
+                for (int c = 0; c < qc && !g.empty(); ++c) (*lost)[(size_t)(q0 + c)] = rest * g[(size_t)c * qc + c];
                 LD_CHECK(adaptive_fused(A, fp, tol, shift, Vq, ld, qc, Pq, ldp, D, b, b.deg + q0, lr, st, launches));
                 continue;
             }
@@ -2214,17 +2231,17 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     LD_CHECK(orthonormalize_and_deflate(A, seed, S, st));
     tm.mark();
     // ---- steps 5 and 6: F [Q_b | U] and the quadratic forms x^T F x
-    std::vector<double> nu((size_t)L.nc, 0.0), g(64 * 64);
+    std::vector<double> nu((size_t)L.nc, 0.0), g(64 * 64), lost;
     for (int blk = 0; blk < L.X.nblocks(); ++blk) {
         const int cols = L.X.bcols(blk), gcol = blk * L.X.bw;
         LD_CHECK(adaptive_apply(A, S.plan, tol, 0.0, L.X.block(blk), L.X.ld, cols, PX.block(blk), L.X.ld, b,
-                                S.longrows, S.resident, st, hdeg, &S.launches23));
+                                S.longrows, S.resident, st, hdeg, &S.launches23, &lost));
         for (int c = 0; c < cols; ++c) deg_all[(size_t)(L.k + gcol + c)] = hdeg[(size_t)c];
         LD_CHECK(cross_product(f64, n, L.X.block(blk), Blk::plain(L.X.ld), cols, PX.block(blk), Blk::plain(L.X.ld),
                                cols, nullptr, b.gpart, b.sums, st));
         LD_CHECK_HIP(hipMemcpyAsync(g.data(), b.sums, (size_t)cols * cols * 8, hipMemcpyDeviceToHost, st));
         LD_CHECK_HIP(hipStreamSynchronize(st));
-        for (int c = 0; c < cols; ++c) nu[(size_t)(gcol + c)] = g[(size_t)c * cols + c];
+        for (int c = 0; c < cols; ++c) nu[(size_t)(gcol + c)] = g[(size_t)c * cols + c] + lost[(size_t)c];
     }
     int hflag[2] = {0, 0};
     LD_CHECK_HIP(hipMemcpyAsync(hflag, S.flag + 1, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
