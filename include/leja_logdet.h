@@ -235,7 +235,10 @@ int ld_squared_basis_coefficients(int32_t degree, const double* d_host, double* 
 /* Bytes of workspace needed by ld_logdet_estimate (want_grad = 0) or
  * ld_logdet_grad (want_grad = 1) for this matrix, degree and query count, or,
  * when n_matvec is negative (-n_matvec = number of columns), by ld_apply_log
- * (want_grad = 0) or ld_apply_log_adaptive (want_grad = 1).
+ * (want_grad = 0) or ld_apply_log_adaptive (want_grad = 1).  The matrix itself
+ * is not read, so the size has room for what its shape admits; the calls accept
+ * less and then take what fits: ld_logdet_estimate a workspace without room for
+ * one column block (see block_cols) on matrices whose columns are scattered.
  * opts may be NULL.  Errors: LD_EINVAL. */
 int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t want_grad,
                       const ld_options* opts, size_t* bytes);

@@ -95,21 +95,32 @@ struct OwnedWs {
     }
 };
 
-int get_workspace(void* ws, size_t ws_bytes, size_t need, OwnedWs& own, Arena& ar) {
+// Device memory of our own; false when there is none (and HIP's record of the
+// failure is cleared: the launches' checks read it).
+bool own_memory(OwnedWs& own, size_t bytes) {
+    if (hipMalloc(&own.p, bytes) == hipSuccess) return true;
+    own.p = nullptr;
+    (void)hipGetLastError();
+    return false;
+}
+
+// The caller's workspace, of at least `least` bytes, or our own: `need` bytes,
+// or `least` where there is no memory for them.
+int get_workspace(void* ws, size_t ws_bytes, size_t least, size_t need, OwnedWs& own, Arena& ar) {
     if (ws) {
         // the carved buffers keep the workspace's alignment, and the step
         // kernels' vector width (hence their grids) assumes 256-byte buffers
         if ((uintptr_t)ws % kAlign != 0) return fail(LD_EINVAL, "workspace must be 256-byte aligned");
-        if (ws_bytes < need)
+        if (ws_bytes < least)
             return fail(LD_EWORKSPACE, "workspace has " + std::to_string(ws_bytes) + " bytes, needs " +
-                                           std::to_string(need));
+                                           std::to_string(least));
         ar.base = (char*)ws;
         ar.size = ws_bytes;
         return LD_OK;
     }
-    if (hipMalloc(&own.p, need) != hipSuccess) return fail(LD_ENOMEM, "hipMalloc of workspace failed");
+    ar.size = own_memory(own, need) ? need : least < need && own_memory(own, least) ? least : 0;
+    if (!own.p) return fail(LD_ENOMEM, "hipMalloc of workspace failed");
     ar.base = (char*)own.p;
-    ar.size = need;
     return LD_OK;
 }
 
@@ -349,7 +360,9 @@ size_t layout_bytes(const EstLayout& L, bool grad) {
 // large as any storage the call may pick needs, and fit_blocks sets the
 // blocks once the storage is known.  The gradient's blocks are fixed (one
 // block each), as are blocks the caller sets.
-EstLayout layout_envelope(const ld_csr* A, int degree, int n_matvec, bool grad, const ld_options& o) {
+// scattered: with room for the one block that scattered columns take.
+EstLayout layout_envelope(const ld_csr* A, int degree, int n_matvec, bool grad, const ld_options& o,
+                          bool scattered = true) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4;
     EstLayout L = layout_estimate(A, degree, n_matvec, grad, o, matrix_bytes(A, elem));
     if (grad || o.block_cols > 0) return L;
@@ -361,7 +374,7 @@ EstLayout layout_envelope(const ld_csr* A, int degree, int n_matvec, bool grad, 
         L.W = std::max(L.W, M.W);
         L.part = std::max(L.part, M.part);
     };
-    cover(kScattered);
+    if (scattered) cover(kScattered);
     if (o.csr_only) return L;
     for (int nd = 1; nd <= kMaxDiag; ++nd)
         for (bool cst : {false, true}) cover(stored_bytes(A, elem, nd, cst));
@@ -1128,8 +1141,10 @@ int carve(Arena& ar, EstLayout& L, EstimateState& S) {
 
 // The column blocks for the storage prepare_rows picked, inside the regions
 // of the envelope the workspace was carved with.
-int fit_blocks(const ld_csr* A, int degree, int n_matvec, const ld_options& o, const LongRows& lr, EstLayout& L) {
-    if (o.block_cols > 0 || (lr.dia_nd <= 0 && !lr.scattered)) return LD_OK;   // the envelope's own blocks
+// one_block: there is room for the block of scattered columns.
+int fit_blocks(const ld_csr* A, int degree, int n_matvec, const ld_options& o, const LongRows& lr, bool one_block,
+               EstLayout& L) {
+    if (o.block_cols > 0 || (lr.dia_nd <= 0 && !(lr.scattered && one_block))) return LD_OK;   // the envelope's own blocks
     const EstLayout M = layout_estimate(
         A, degree, n_matvec, false, o,
         lr.dia_nd > 0 ? stored_bytes(A, L.elem, lr.dia_nd, lr.dia_pres != nullptr) : kScattered);
@@ -1622,6 +1637,9 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
     EstimateState S;
     S.timed = timed;
     LD_CHECK(make_plan(lmin, lmax, degree, o, S.plan));
+    // a workspace without room for the one block of scattered columns keeps the
+    // blocks that follow the stored bytes
+    const EstLayout least = layout_envelope(A, degree, n_matvec, want_grad, o, false);
     S.L = layout_envelope(A, degree, n_matvec, want_grad, o);
     S.mode = choose_dot_mode(S.plan, o.dot_mode, S.coef);
     if (o.probe_dist != LD_PROBE_RADEMACHER && o.probe_dist != LD_PROBE_GAUSSIAN)
@@ -1629,7 +1647,10 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
     S.probe = o.probe_dist;
     OwnedWs own;
     Arena ar;
-    LD_CHECK(get_workspace(workspace, ws_bytes, layout_bytes(S.L, want_grad), own, ar));
+    LD_CHECK(get_workspace(workspace, ws_bytes, layout_bytes(least, want_grad), layout_bytes(S.L, want_grad), own,
+                           ar));
+    const bool one_block = ar.size >= layout_bytes(S.L, want_grad);
+    if (!one_block) S.L = least;
     carve(ar, S.L, S);
     GradBufs B;
     // the squared path takes [Q_b | U] as one block of at most 64 columns (one
@@ -1664,7 +1685,7 @@ int run_logdet(const ld_csr* A, double lmin, double lmax, int degree, int n_matv
         return fail(LD_EINVAL, "internal: workspace layout overflow");
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
     if (!want_grad) {
-        LD_CHECK(fit_blocks(A, degree, n_matvec, o, S.longrows, S.L));
+        LD_CHECK(fit_blocks(A, degree, n_matvec, o, S.longrows, one_block, S.L));
         S.resident = resident_fits(A, S.longrows, o, degree);
         S.fused_D = S.resident ? 0 : fused_line(A, S.longrows);
         if (S.fused_D) {
@@ -2192,7 +2213,7 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     // a workspace without the blocks of chunks takes one launch per step
     const size_t plain = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, false);
     const size_t with_chunks = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, true);
-    LD_CHECK(get_workspace(workspace, ws_bytes, workspace ? plain : with_chunks, own, ar));
+    LD_CHECK(get_workspace(workspace, ws_bytes, plain, with_chunks, own, ar));
     carve(ar, S.L, S);
     const EstLayout& L = S.L;
     BlkMat PX = L.X;   // F [Q_b | U], the layout of X
@@ -2368,7 +2389,8 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
     const bool room = with_pack > 0 && (!workspace || ws_bytes >= with_pack);
     OwnedWs own;
     Arena ar;
-    LD_CHECK(get_workspace(workspace, ws_bytes, room ? std::max(plain, with_pack) : plain, own, ar));
+    const size_t need = room ? std::max(plain, with_pack) : plain;
+    LD_CHECK(get_workspace(workspace, ws_bytes, need, need, own, ar));
     const int v = 16 / (int)elem, ldp = padded_ld(nc, (int)elem);
     const size_t pblk = (size_t)n * ldp * elem;
     void* const B0 = ar.take(room ? pblk : blk);
@@ -2479,7 +2501,7 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     OwnedWs own;
     Arena ar;
     const size_t with_chunks = adaptive_ws_bytes(A, nc, o, true);   // without: one launch per step
-    LD_CHECK(get_workspace(workspace, ws_bytes, workspace ? adaptive_ws_bytes(A, nc, o, false) : with_chunks, own, ar));
+    LD_CHECK(get_workspace(workspace, ws_bytes, adaptive_ws_bytes(A, nc, o, false), with_chunks, own, ar));
     AdaptBufs b;
     b.W[0] = ar.take(blk);
     b.W[1] = ar.take(blk);
@@ -2540,7 +2562,7 @@ int ld_logdet_estimate_noalloc(const ld_csr* A, double lmin, double lmax, int32_
     if (!out_logdet) return fail(LD_EINVAL, "out_logdet is null");
     LD_CHECK(check_estimate_args(A, lmin, lmax, degree, n_matvec));
     const ld_options o = resolve(opts);
-    const size_t need = layout_bytes(layout_envelope(A, degree, n_matvec, false, o), false);
+    const size_t need = layout_bytes(layout_envelope(A, degree, n_matvec, false, o, false), false);
     if (need > kNoAllocScratchBytes)
         return fail(LD_EWORKSPACE, "the estimate needs " + std::to_string(need) +
                                        " bytes of scratch; the library's static scratch holds " +
