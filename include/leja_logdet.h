@@ -238,7 +238,10 @@ int ld_squared_basis_coefficients(int32_t degree, const double* d_host, double* 
  * (want_grad = 0) or ld_apply_log_adaptive (want_grad = 1).  The matrix itself
  * is not read, so the size has room for what its shape admits; the calls accept
  * less and then take what fits: ld_logdet_estimate a workspace without room for
- * one column block (see block_cols) on matrices whose columns are scattered.
+ * one column block (see block_cols) on matrices whose columns are scattered,
+ * ld_apply_log one of two blocks as V is stored (besides the preparation) in
+ * place of three packed ones, ld_apply_log_adaptive one without room for the
+ * launches of several steps (its size with any tile_order but auto).
  * opts may be NULL.  Errors: LD_EINVAL. */
 int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t want_grad,
                       const ld_options* opts, size_t* bytes);
@@ -271,7 +274,9 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
                           void* workspace, size_t ws_bytes, void* stream, int32_t* degrees);
 
 /* Bytes of workspace needed by ld_logdet_estimate_adaptive for this matrix,
- * largest degree and query count.  opts may be NULL.  Errors: LD_EINVAL. */
+ * largest degree and query count.  A workspace without room for the launches of
+ * several steps (the size with any tile_order but auto) is accepted and takes
+ * one launch per step.  opts may be NULL.  Errors: LD_EINVAL. */
 int ld_adaptive_workspace_size(const ld_csr* A, int32_t max_degree, int32_t n_matvec,
                                const ld_options* opts, size_t* bytes);
 

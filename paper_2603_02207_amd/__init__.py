@@ -144,6 +144,19 @@ def _workspace(nbytes: int, device):
     return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
+def _with_workspace(nbytes: int, device, call) -> int:
+    """call(pointer, bytes) with a workspace of nbytes; where PyTorch has no memory for it, with none: the library
+    then allocates what the matrix needs, or the least it accepts (nbytes is what its shape alone may need)."""
+    try:
+        ws = _workspace(nbytes, device)
+    except _torch().OutOfMemoryError:
+        rc = call(None, 0)
+        if rc == nat.LD_ENOMEM:
+            raise
+        return rc
+    return call(ws.data_ptr(), ws.numel())
+
+
 def logdet(A: CSR, lmin: float, lmax: float, degree: int, n_matvec: int, seed: int = 0,
            options=None, return_stats: bool = False, workspace=None):
     """Léja + Hutch++ estimate of log det A (Alg. 3); a Python float."""
@@ -151,14 +164,18 @@ def logdet(A: CSR, lmin: float, lmax: float, degree: int, n_matvec: int, seed: i
     c = A.c_struct()
     o = _opts(options)
     need = workspace_size(A, degree, n_matvec, False, options)
-    ws = workspace if workspace is not None and workspace.numel() >= need else _workspace(need, A.val.device)
     out = ctypes.c_double(0.0)
     st = nat.LdStats()
-    nat.check(lib.ld_logdet_estimate(ctypes.byref(c), float(lmin), float(lmax), int(degree),
-                                     int(n_matvec), ctypes.c_uint64(int(seed) & (2**64 - 1)),
-                                     ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
-                                     _stream_handle(A.val.device), ctypes.byref(out),
-                                     ctypes.byref(st) if return_stats else None), "ld_logdet_estimate")
+
+    def call(ptr, nbytes):
+        return lib.ld_logdet_estimate(ctypes.byref(c), float(lmin), float(lmax), int(degree),
+                                      int(n_matvec), ctypes.c_uint64(int(seed) & (2**64 - 1)),
+                                      ctypes.byref(o), ctypes.c_void_p(ptr), nbytes,
+                                      _stream_handle(A.val.device), ctypes.byref(out),
+                                      ctypes.byref(st) if return_stats else None)
+
+    nat.check(call(workspace.data_ptr(), workspace.numel()) if workspace is not None and workspace.numel() >= need
+              else _with_workspace(need, A.val.device, call), "ld_logdet_estimate")
     if return_stats:
         return out.value, st.as_dict()
     return out.value
@@ -175,15 +192,14 @@ def logdet_adaptive(A: CSR, lmin: float, lmax: float, max_degree: int, tol: floa
     b = ctypes.c_size_t(0)
     nat.check(lib.ld_adaptive_workspace_size(ctypes.byref(c), int(max_degree), int(n_matvec), ctypes.byref(o),
                                              ctypes.byref(b)), "ld_adaptive_workspace_size")
-    ws = _workspace(int(b.value), A.val.device)
     out = ctypes.c_double(0.0)
     st = nat.LdStats()
     degrees = np.zeros(int(n_matvec), dtype=np.int32)
-    nat.check(lib.ld_logdet_estimate_adaptive(
+    nat.check(_with_workspace(int(b.value), A.val.device, lambda ptr, nbytes: lib.ld_logdet_estimate_adaptive(
         ctypes.byref(c), float(lmin), float(lmax), int(max_degree), float(tol), int(n_matvec),
-        ctypes.c_uint64(int(seed) & (2**64 - 1)), ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+        ctypes.c_uint64(int(seed) & (2**64 - 1)), ctypes.byref(o), ctypes.c_void_p(ptr), nbytes,
         _stream_handle(A.val.device), ctypes.byref(out), degrees.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
-        ctypes.byref(st) if return_stats else None), "ld_logdet_estimate_adaptive")
+        ctypes.byref(st) if return_stats else None)), "ld_logdet_estimate_adaptive")
     if return_stats:
         return out.value, degrees, st.as_dict()
     return out.value, degrees
@@ -287,11 +303,10 @@ def apply_log(A: CSR, lmin: float, lmax: float, degree: int, V, options=None):
     b = ctypes.c_size_t(0)
     nat.check(lib.ld_workspace_size(ctypes.byref(c), int(degree), -int(V.shape[1]), 0,
                                     ctypes.byref(o), ctypes.byref(b)), "ld_workspace_size")
-    ws = _workspace(int(b.value), V.device)
-    nat.check(lib.ld_apply_log(ctypes.byref(c), float(lmin), float(lmax), int(degree),
-                               ctypes.c_void_p(V.data_ptr()), ctypes.c_void_p(out.data_ptr()),
-                               int(V.shape[1]), ctypes.byref(o), ctypes.c_void_p(ws.data_ptr()),
-                               ws.numel(), _stream_handle(V.device)), "ld_apply_log")
+    nat.check(_with_workspace(int(b.value), V.device, lambda ptr, nbytes: lib.ld_apply_log(
+        ctypes.byref(c), float(lmin), float(lmax), int(degree), ctypes.c_void_p(V.data_ptr()),
+        ctypes.c_void_p(out.data_ptr()), int(V.shape[1]), ctypes.byref(o), ctypes.c_void_p(ptr), nbytes,
+        _stream_handle(V.device))), "ld_apply_log")
     return out
 
 
@@ -308,18 +323,21 @@ def apply_log_adaptive(A: CSR, lmin: float, lmax: float, max_degree: int, tol: f
     degrees = np.zeros(ncols, dtype=np.int32)
     c = A.c_struct()
     o = _opts(options)
-    ws = None
+
+    def call(ptr, nbytes):
+        return lib.ld_apply_log_adaptive(
+            ctypes.byref(c), float(lmin), float(lmax), int(max_degree), float(tol),
+            ctypes.c_void_p(V.data_ptr() if ncols else None), ctypes.c_void_p(out.data_ptr() if ncols else None),
+            ncols, ctypes.byref(o), ctypes.c_void_p(ptr), nbytes, _stream_handle(V.device),
+            degrees.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
+
     if ncols > 0:
         b = ctypes.c_size_t(0)
         nat.check(lib.ld_workspace_size(ctypes.byref(c), int(max_degree), -ncols, 1, ctypes.byref(o),
                                         ctypes.byref(b)), "ld_workspace_size")
-        ws = _workspace(int(b.value), V.device)
-    nat.check(lib.ld_apply_log_adaptive(
-        ctypes.byref(c), float(lmin), float(lmax), int(max_degree), float(tol),
-        ctypes.c_void_p(V.data_ptr() if ncols else None), ctypes.c_void_p(out.data_ptr() if ncols else None),
-        ncols, ctypes.byref(o), ctypes.c_void_p(ws.data_ptr() if ws is not None else None),
-        ws.numel() if ws is not None else 0, _stream_handle(V.device),
-        degrees.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))), "ld_apply_log_adaptive")
+        nat.check(_with_workspace(int(b.value), V.device, call), "ld_apply_log_adaptive")
+    else:
+        nat.check(call(None, 0), "ld_apply_log_adaptive")
     return out, degrees
 
 

@@ -521,6 +521,12 @@ int fused_line(const ld_csr* A, const LongRows& lr) {
     return A->n + (long long)(2 * kFusedMax + 4) * D < (1ll << 31) ? D : 0;
 }
 
+// Whether a matrix of this size, under these options, may turn out to take them
+// (a question of room: a pentadiagonal matrix has as many entries).
+bool may_fuse(const ld_csr* A, const ld_options& o) {
+    return o.tile_order == LD_TILES_AUTO && !o.csr_only && A->n > kFusedMinWidth && A->nnz <= 5 * A->n;
+}
+
 // A block as the fused launches address it: rows of a row-major block, or
 // 16-byte column chunks one after another (the work blocks between launches).
 struct FusedBlock {
@@ -1926,25 +1932,35 @@ static_assert(kAdaptWords * 8 + 4 <= 256, "the mask's 256 bytes");
 
 // Bytes of one of adaptive_fused's four blocks of chunks; 0 when the matrix
 // cannot qualify or a block would be beyond kPackMost (no room is asked for).
-size_t adaptive_chunk_bytes(const ld_csr* A, int ncols) {
+size_t adaptive_chunk_bytes(const ld_csr* A, int ncols, const ld_options& o) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4;
     const size_t blk = align_up((size_t)A->n * padded_ld(std::min(ncols, 64), (int)elem) * elem);
-    return A->n > kFusedMinWidth && A->nnz <= 5 * A->n && blk <= kPackMost ? blk : 0;
+    return may_fuse(A, o) && blk <= kPackMost ? blk : 0;
 }
 
-// Takes them from the workspace (which has room); W0 and W1 serve as two of
-// them where they are long enough.
-void take_chunks(Arena& ar, const ld_csr* A, int ncols, size_t wbytes, AdaptBufs& b) {
-    const size_t blk = adaptive_chunk_bytes(A, ncols);
-    if (blk == 0) return;
-    for (int i = 0; i < 4; ++i) b.chunks[i] = i < 2 && wbytes >= blk ? b.W[i] : ar.take(blk);
+// W0 and W1 (wbytes each) serve as two of them where they are long enough.
+size_t adaptive_chunks_bytes(size_t blk, size_t wbytes) { return (wbytes >= blk ? 2 : 4) * blk; }
+
+// Takes them, for a matrix that turned out to qualify: from the caller's
+// workspace when it has room, else, in a call that allocates its own memory,
+// from `own` (no memory: one launch per step, as without room).
+void take_chunks(Arena& ar, bool room, bool callers, const ld_csr* A, const LongRows& lr, int ncols, size_t wbytes,
+                 const ld_options& o, OwnedWs& own, AdaptBufs& b) {
+    const size_t blk = adaptive_chunk_bytes(A, ncols, o);
+    if (blk == 0 || !fused_line(A, lr)) return;
+    Arena mine;
+    if (!room) {
+        if (callers || !own_memory(own, adaptive_chunks_bytes(blk, wbytes))) return;
+        mine.base = (char*)own.p;
+    }
+    for (int i = 0; i < 4; ++i) b.chunks[i] = i < 2 && wbytes >= blk ? b.W[i] : (room ? ar : mine).take(blk);
 }
 
 size_t adaptive_ws_bytes(const ld_csr* A, int ncols, const ld_options& o, bool chunked) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4;
     const int n = (int)A->n;
-    const size_t w = align_up((size_t)n * ncols * elem), chunk = adaptive_chunk_bytes(A, ncols);
-    return (chunked ? (w >= chunk ? 2 : 4) * chunk : 0) + 2 * w +
+    const size_t w = align_up((size_t)n * ncols * elem);
+    return (chunked ? adaptive_chunks_bytes(adaptive_chunk_bytes(A, ncols, o), w) : 0) + 2 * w +
            align_up((size_t)step_num_wg_any(n) * 64 * 8) +
            align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + align_up(256) +
            align_up((size_t)ncols * 4) + align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
@@ -2190,8 +2206,8 @@ EstLayout layout_adaptive(const ld_csr* A, int max_degree, int n_matvec, const l
 size_t adaptive_estimate_ws_bytes(const ld_csr* A, int max_degree, int n_matvec, const ld_options& o, bool chunked) {
     const EstLayout L = layout_adaptive(A, max_degree, n_matvec, o);
     const int n = (int)A->n;
-    const size_t chunk = chunked ? adaptive_chunk_bytes(A, std::max(L.Y.bw, L.X.bw)) : 0;
-    return layout_bytes(L, false) + (L.W >= chunk ? 2 : 4) * chunk + align_up(L.xb) + align_up((size_t)step_num_wg_any(n) * 64 * 8) +
+    const size_t chunk = chunked ? adaptive_chunk_bytes(A, std::max(L.Y.bw, L.X.bw), o) : 0;
+    return layout_bytes(L, false) + adaptive_chunks_bytes(chunk, L.W) + align_up(L.xb) + align_up((size_t)step_num_wg_any(n) * 64 * 8) +
            align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + 2 * align_up(256) + 256;
 }
 
@@ -2208,12 +2224,11 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     if (o.probe_dist != LD_PROBE_RADEMACHER && o.probe_dist != LD_PROBE_GAUSSIAN)
         return fail(LD_EINVAL, "probe_dist must be LD_PROBE_RADEMACHER or LD_PROBE_GAUSSIAN");
     S.probe = o.probe_dist;
-    OwnedWs own;
+    OwnedWs own, own_chunks;
     Arena ar;
     // a workspace without the blocks of chunks takes one launch per step
     const size_t plain = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, false);
-    const size_t with_chunks = adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, true);
-    LD_CHECK(get_workspace(workspace, ws_bytes, plain, with_chunks, own, ar));
+    LD_CHECK(get_workspace(workspace, ws_bytes, plain, plain, own, ar));
     carve(ar, S.L, S);
     const EstLayout& L = S.L;
     BlkMat PX = L.X;   // F [Q_b | U], the layout of X
@@ -2227,9 +2242,11 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take(256);   // one block's columns (at most 64)
     if (ar.used > plain) return fail(LD_EINVAL, "internal: workspace layout overflow");
-    if (ar.size >= with_chunks) take_chunks(ar, A, std::max(L.Y.bw, L.X.bw), L.W, b);
     LD_CHECK(prepare_rows(A, o, ar, st, S.longrows));
     S.resident = resident_fits(A, S.longrows, o, max_degree);
+    if (!S.resident)
+        take_chunks(ar, ar.size >= adaptive_estimate_ws_bytes(A, max_degree, n_matvec, o, true), workspace != nullptr, A,
+                    S.longrows, std::max(L.Y.bw, L.X.bw), L.W, o, own_chunks, b);
     Timer tm(st, stats != nullptr);
     tm.mark();
     std::vector<int> deg_all((size_t)n_matvec, 0), hdeg;
@@ -2306,19 +2323,24 @@ int run_logdet_adaptive(const ld_csr* A, double lmin, double lmax, int max_degre
 }
 
 // Rows of V that are no whole number of 16-byte vectors (three columns or more:
-// fewer move less as they are) go through padded copies: the steps' vector
-// accesses outweigh the two copies from a few steps on.  Diagonal storage always
-// gains (us per step, as V is, padded: pentadiagonal, 500000 rows, 17 FP32 columns
-// 45.6, 24.7).  CSR rows, fewer lanes to a padded row, may lose the staging of
-// their entries that V's own rows have (step_staging): band of 8, 600000 rows, 7
-// FP64 columns (7 lanes, 4 padded) 57, 83; 100000 rows, 9 FP32 (9 lanes, 3) 10.4,
-// 15.5; 27-point grid 64^3, 13 FP64 (13 lanes, 7) 69, 88.  Such rows stay as they
-// are, but for one or two lanes (7 FP32 columns 41.9, 36.7 at 600000 rows), long
-// own rows (13 FP32 columns on 4 lanes, mesh of 300000 rows 52.7, 32.7; 17 on 5
-// from about 140000 rows on) and very few tiles, where slices make up for it.
+// fewer move less as they are) may go through padded copies: the steps' vector
+// accesses outweigh the two copies from a few steps on.
+bool may_pad(const ld_csr* A, int64_t ncols, int degree, const ld_options& o) {
+    return o.block_cols <= 0 && ncols >= 3 && ncols % (A->dtype == LD_F64 ? 2 : 4) != 0 && degree >= 4;
+}
+
+// Whether they do.  Diagonal storage always gains (us per step, as V is, padded:
+// pentadiagonal, 500000 rows, 17 FP32 columns 45.6, 24.7).  CSR rows, fewer lanes
+// to a padded row, may lose the staging of their entries that V's own rows have
+// (step_staging): band of 8, 600000 rows, 7 FP64 columns (7 lanes, 4 padded) 57,
+// 83; 100000 rows, 9 FP32 (9 lanes, 3) 10.4, 15.5; 27-point grid 64^3, 13 FP64 (13
+// lanes, 7) 69, 88.  Such rows stay as they are, but for one or two lanes (7 FP32
+// columns 41.9, 36.7 at 600000 rows), long own rows (13 FP32 columns on 4 lanes,
+// mesh of 300000 rows 52.7, 32.7; 17 on 5 from about 140000 rows on) and very few
+// tiles, where slices make up for it.
 bool pads_rows(const ld_csr* A, const LongRows& lr, const ld_options& o, int nc, int degree) {
     const int v = A->dtype == LD_F64 ? 2 : 4;
-    if (o.block_cols > 0 || nc < 3 || nc % v == 0 || degree < 4) return false;
+    if (!may_pad(A, nc, degree, o)) return false;
     if (lr.dia_nd > 0 || lr.interleaved()) return true;
     int vown = v;
     while (nc % vown) vown /= 2;
@@ -2330,16 +2352,27 @@ bool pads_rows(const ld_csr* A, const LongRows& lr, const ld_options& o, int nc,
     return staging(pad) <= 0.9 || pad <= 2 || tiles < 256 || (own > 10 && (pad < 5 || tiles >= 1100));
 }
 
-// Workspace of ld_apply_log: two blocks as V is stored, or, packed, V and two
-// blocks with rows padded to whole 16-byte vectors (not asked for above
-// kPackMost bytes a block).
-
-size_t apply_ws_bytes(const ld_csr* A, int64_t ncols, const ld_options& o, bool packed) {
+// ld_apply_log's blocks: two as V is stored, or, packed, V and two blocks with
+// rows padded to whole 16-byte vectors (0 above kPackMost bytes a block).
+size_t apply_block_bytes(const ld_csr* A, int64_t ncols) {
+    return align_up((size_t)A->n * (size_t)ncols * (A->dtype == LD_F64 ? 8 : 4));
+}
+size_t packed_block_bytes(const ld_csr* A, int64_t ncols) {
     const size_t elem = A->dtype == LD_F64 ? 8 : 4, v = 16 / elem;
-    const size_t rest = align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
-    if (!packed) return 2 * align_up((size_t)A->n * (size_t)ncols * elem) + rest;
     const size_t blk = align_up((size_t)A->n * (((size_t)ncols + v - 1) / v * v) * elem);
-    return blk <= kPackMost ? 3 * blk + rest : 0;
+    return blk <= kPackMost ? blk : 0;
+}
+
+// Workspace besides the blocks: the matrix preparation.
+size_t apply_rest_bytes(const ld_csr* A, const ld_options& o) {
+    return align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+}
+
+// Workspace that no path of the call can do more with.
+size_t apply_ws_bytes(const ld_csr* A, int64_t ncols, int degree, const ld_options& o) {
+    const bool may_pack = may_pad(A, ncols, degree, o) || (o.block_cols <= 0 && may_fuse(A, o));
+    return std::max(2 * apply_block_bytes(A, ncols), may_pack ? 3 * packed_block_bytes(A, ncols) : 0) +
+           apply_rest_bytes(A, o);
 }
 
 extern "C" {
@@ -2356,7 +2389,7 @@ int ld_workspace_size(const ld_csr* A, int32_t degree, int32_t n_matvec, int32_t
         return LD_OK;
     }
     if (n_matvec < 0) {
-        *bytes = std::max(apply_ws_bytes(A, -(int64_t)n_matvec, o, false), apply_ws_bytes(A, -(int64_t)n_matvec, o, true));
+        *bytes = apply_ws_bytes(A, -(int64_t)n_matvec, degree, o);
         return LD_OK;
     }
     if (n_matvec < 3) return fail(LD_EINVAL, "n_matvec must be >= 3");
@@ -2384,24 +2417,30 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
     const uint8_t* v8 = (const uint8_t*)V;
     const uint8_t* p8 = (const uint8_t*)PV;
     if (v8 < p8 + blk && p8 < v8 + blk) return fail(LD_EINVAL, "V and PV overlap");
-    // a workspace of the size without the packed blocks keeps V's own layout
-    const size_t plain = apply_ws_bytes(A, ncols, o, false), with_pack = apply_ws_bytes(A, ncols, o, true);
-    const bool room = with_pack > 0 && (!workspace || ws_bytes >= with_pack);
-    OwnedWs own;
+    // the preparation first: it says which blocks the matrix needs
+    const size_t rest = apply_rest_bytes(A, o), vblk = apply_block_bytes(A, ncols), pblk = packed_block_bytes(A, ncols);
+    OwnedWs own, own_blocks;
     Arena ar;
-    const size_t need = room ? std::max(plain, with_pack) : plain;
-    LD_CHECK(get_workspace(workspace, ws_bytes, need, need, own, ar));
-    const int v = 16 / (int)elem, ldp = padded_ld(nc, (int)elem);
-    const size_t pblk = (size_t)n * ldp * elem;
-    void* const B0 = ar.take(room ? pblk : blk);
-    void* const B1 = ar.take(room ? pblk : blk);
-    void* const B2 = room ? ar.take(pblk) : nullptr;
-    (void)ar.take(256);
+    const size_t least = workspace ? rest + 2 * vblk : rest;
+    LD_CHECK(get_workspace(workspace, ws_bytes, least, least, own, ar));
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
-    const int m = p.degree;
+    const int v = 16 / (int)elem, ldp = padded_ld(nc, (int)elem), m = p.degree;
+    const bool resident = resident_fits(A, lr, o, m);   // needs no blocks
+    const int line = !resident && o.block_cols <= 0 ? fused_line(A, lr) : 0;
+    bool packed = !resident && pblk > 0 && (line || pads_rows(A, lr, o, nc, m));
+    if (workspace) {   // one without room for the packed blocks keeps V's own layout
+        packed = packed && ar.size - rest >= 3 * pblk;
+    } else if (!resident) {
+        packed = packed && own_memory(own_blocks, 3 * pblk);
+        if (!packed && !own_memory(own_blocks, 2 * vblk)) return fail(LD_ENOMEM, "hipMalloc of workspace failed");
+        ar = Arena{(char*)own_blocks.p, packed ? 3 * pblk : 2 * vblk, 0};
+    }
+    void* const B0 = resident ? nullptr : ar.take(packed ? pblk : vblk);
+    void* const B1 = resident ? nullptr : ar.take(packed ? pblk : vblk);
+    void* const B2 = packed ? ar.take(pblk) : nullptr;
     const double d0 = p.d[0] + std::log(p.sigma);
-    if (resident_fits(A, lr, o, m)) {
+    if (resident) {
         ResidentArgs f{};
         f.kind = STEP_HORNER_VEC;
         f.cols = nc;
@@ -2418,7 +2457,7 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
         f.beta = beta.data();
         f.d = d.data();
         LD_CHECK_HIP(launch_resident(f64, dev_of(A), f, st));
-    } else if (const int D = room && o.block_cols <= 0 ? fused_line(A, lr) : 0) {
+    } else if (const int D = packed ? line : 0) {
         // column groups whose V and two work blocks fit the Infinity Cache, each
         // through its whole recurrence; V's chunks are read by every launch
         const bool whole = nc == v && (uintptr_t)V % 16 == 0 && (uintptr_t)PV % 16 == 0;   // V is one chunk already
@@ -2445,7 +2484,7 @@ int ld_apply_log(const ld_csr* A, double lmin, double lmax, int32_t degree, cons
         }
         if (!whole) LD_CHECK_HIP(launch_unpack_chunks(f64, n, nc, B0, PV, nc, st));
     } else {
-        const bool pad = room && pads_rows(A, lr, o, nc, m);
+        const bool pad = packed;
         const int ld = pad ? ldp : nc;
         const void* src = V;
         if (pad) {
@@ -2498,10 +2537,10 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     const uint8_t* v8 = (const uint8_t*)V;
     const uint8_t* p8 = (const uint8_t*)PV;
     if (v8 < p8 + blk && p8 < v8 + blk) return fail(LD_EINVAL, "V and PV overlap");
-    OwnedWs own;
+    OwnedWs own, own_chunks;
     Arena ar;
-    const size_t with_chunks = adaptive_ws_bytes(A, nc, o, true);   // without: one launch per step
-    LD_CHECK(get_workspace(workspace, ws_bytes, adaptive_ws_bytes(A, nc, o, false), with_chunks, own, ar));
+    const size_t plain = adaptive_ws_bytes(A, nc, o, false);   // without the chunks: one launch per step
+    LD_CHECK(get_workspace(workspace, ws_bytes, plain, plain, own, ar));
     AdaptBufs b;
     b.W[0] = ar.take(blk);
     b.W[1] = ar.take(blk);
@@ -2511,12 +2550,14 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take((size_t)nc * 4);
     (void)ar.take(256);
-    if (ar.size >= with_chunks) take_chunks(ar, A, nc, align_up(blk), b);
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
+    const bool resident = resident_fits(A, lr, o, p.degree);
+    if (!resident)
+        take_chunks(ar, ar.size >= adaptive_ws_bytes(A, nc, o, true), workspace != nullptr, A, lr, nc, align_up(blk), o,
+                    own_chunks, b);
     std::vector<int> hdeg;
-    LD_CHECK(adaptive_apply(A, p, tol, std::log(p.sigma), V, nc, nc, PV, nc, b, lr,
-                            resident_fits(A, lr, o, p.degree), st, hdeg, nullptr));
+    LD_CHECK(adaptive_apply(A, p, tol, std::log(p.sigma), V, nc, nc, PV, nc, b, lr, resident, st, hdeg, nullptr));
     if (degrees)
         for (int c = 0; c < nc; ++c) degrees[c] = hdeg[(size_t)c];
     return LD_OK;
