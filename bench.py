@@ -32,6 +32,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "logdet estimates/sec & SpMM HBM GB/s at ≤1e-4 rel err, FP32 vs FP64, 1 GPU"
 HBM_PEAK_GBS = 8000.0
+# FP32 vector products without packed instructions: 256 CUs x 64 lanes x 2 flops x 2.4 GHz
+VALU_PEAK_TFLOPS = 78.6
+FUSED_MAX_STEPS = 6   # most steps of one launch on five-point stencils
 INFINITY_CACHE_BYTES = 256e6   # MI355X last-level (MALL) cache: a launch below this can run from it
 LARGE_WORKLOADS = {           # extra records of the default line
     "gmrf2048": "gmrf2048",        # the 2048^2 GMRF: column blocks that fit the Infinity Cache
@@ -293,10 +296,13 @@ def steps_per_launch(tag: str, st) -> float:
 
 def step_kernel_name(tag: str, st) -> str:
     """Kernel of a phase's Newton steps: one launch for several of them on
-    constant five-point stencils; on other diagonal storage the sketch's
-    steps (no column sums) take the one-chunk-per-thread kernel."""
-    if steps_per_launch(tag, st) > 1:
-        return "fused_kernel"
+    constant five-point stencils, for all of them on matrices that fit a CU's
+    LDS; on other diagonal storage the sketch's steps (no column sums) take
+    the one-chunk-per-thread kernel."""
+    steps = steps_per_launch(tag, st)
+    if steps > 1:
+        stencil = st.get("dia_diagonals") == 5 and st.get("dia_constant")
+        return "fused_kernel" if stencil and steps <= FUSED_MAX_STEPS else "resident_kernel"
     return "dia_flat_kernel" if tag == "sketch_horner" and st.get("dia_diagonals") else "step_kernel"
 
 
@@ -526,11 +532,47 @@ def kernel_records(st):
 
 
 def step_bound(rec) -> str:
-    """What bounds a phase's launches: several steps in one are bound by the vector ALUs (the block moves once
-    per launch), beyond the Infinity Cache by both."""
+    """What bounds a phase's launches.  Several steps in one: the vector ALUs (by counters busy for 73% of a sketch
+    launch and 55% of one of the quadratic forms at 1024^2 points, profiles/fused_kernel_grid1024_valu.md; the rest
+    is latency at 2.2 to 2.6 waves a SIMD), at any size: 5000^2 points take the same time per element.  All steps of
+    a small matrix in one: the LDS reads of a row's neighbours, one after another, and two barriers a step."""
     if rec["kernel"] == "fused_kernel":
-        return "valu" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "valu and hbm"
+        return "valu"
+    if rec["kernel"] == "resident_kernel":
+        return "lds_latency"
     return "infinity_cache" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
+
+
+def step_tflops(tag, rec, st, nnz) -> float:
+    """Useful TFLOP/s of a phase: a product with A per step and column, and per element the probe's term (sketch) or
+    the two column sums."""
+    cols = st["k"] if tag == "sketch_horner" else st["k"] + st["k_G"]
+    steps = rec["steps_per_launch"] * rec["launches"] / -(-cols // st["block_cols1" if tag == "sketch_horner" else "block_cols23"])
+    return steps * cols * (2.0 * nnz + (1.0 if tag == "sketch_horner" else 4.0) * st["n"]) / (rec["total_ms"] * 1e9)
+
+
+def roofline(tag, rec, st, nnz):
+    """The rate of a phase's step kernel in the unit of what bounds it."""
+    bound = step_bound(rec)
+    if rec["kernel"] in ("fused_kernel", "resident_kernel"):
+        achieved, peak, unit = step_tflops(tag, rec, st, nnz), VALU_PEAK_TFLOPS, "TFLOP/s"
+    else:
+        achieved, peak, unit = rec["GBps"], HBM_PEAK_GBS, "GB/s"
+    return {"bound": bound, "kernel": f"{rec['kernel']} ({tag})", "achieved": achieved, "peak": peak, "unit": unit,
+            "frac": achieved / peak, "launch_GBps": rec["GBps"]}
+
+
+def working_set(rec) -> str:
+    mb = f"{rec['bytes_per_launch'] / 1e6:.0f} MB per launch "
+    if rec["kernel"] == "fused_kernel":
+        return mb + (f"of {rec['steps_per_launch']:.1f} steps: the block moves once per launch, so bytes do not bound "
+                     "it; peak: FP32 vector products without packed instructions")
+    if rec["kernel"] == "resident_kernel":
+        return mb + "of all steps, from and to LDS and registers"
+    if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES:
+        return mb + ("<= the 256 MB Infinity Cache: the blocks stream from the cache, so frac against the HBM peak "
+                     "is not an HBM efficiency (hbm_bound: a workload whose blocks cannot fit it)")
+    return mb + "> the 256 MB Infinity Cache: the blocks stream from HBM"
 
 
 def run_workload(args, workload, steps):
@@ -585,14 +627,10 @@ def run_workload(args, workload, steps):
     # dominant recurrence kernel, timed by HIP events on the launch stream
     kernels = kernel_records({**st, "degree": cfg["degree"]})
     dom = max(kernels, key=lambda k: kernels[k]["total_ms"])
-    achieved = kernels[dom]["GBps"]
     traffic = (measured_traffic(dom, args.workload, kernels[dom]["kernel"])
                if args.block_cols == 0 and args.dot_mode == "auto" else None)
     total_bytes = st["bytes1"] + st["bytes23"]
     total_ms = st["ms_steps1"] + st["ms_steps23"]
-    # a launch whose bytes fit the Infinity Cache streams (largely) from it:
-    # its GB/s is then not an HBM bandwidth
-    in_cache = kernels[dom]["bytes_per_launch"] <= INFINITY_CACHE_BYTES
     method = method_bytes_per_estimate(n, nnz, degree, st["k"], st["k_G"])
 
     out = {
@@ -631,20 +669,11 @@ def run_workload(args, workload, steps):
             "parallelism": "single GPU",
         },
         "roofline": {
-            "bound": step_bound(kernels[dom]),
-            "kernel": f"{kernels[dom]['kernel']} ({dom})",
-            "achieved": achieved,
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
+            **roofline(dom, kernels[dom], {**st, "n": n}, nnz),
             "traffic": traffic,
             "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "alg_bytes_per_launch": kernels[dom]["bytes_per_launch"],
-            "working_set": (f"{kernels[dom]['bytes_per_launch'] / 1e6:.0f} MB per launch "
-                            + ("<= the 256 MB Infinity Cache: the blocks stream from the cache, so frac "
-                               "against the HBM peak is not an HBM efficiency (hbm_bound: a workload whose "
-                               "blocks cannot fit it)" if in_cache
-                               else "> the 256 MB Infinity Cache: the blocks stream from HBM")),
+            "working_set": working_set(kernels[dom]),
         },
         "spmm_recurrence_GBps": total_bytes / (total_ms / 1e3) / 1e9,
         "kernels": kernels,
@@ -804,6 +833,7 @@ def large_record(args, name):
         "column_blocks": {"sketch": st["block_cols1"], "quadform": st["block_cols23"]},
         "dominant_kernel": f"{kernels[dom]['kernel']} ({dom})",
         "bound": step_bound(kernels[dom]),
+        "roofline": roofline(dom, kernels[dom], {**st, "n": n}, nnz),
         "avg_us": kernels[dom]["avg_us"],
         "alg_bytes_per_launch": kernels[dom]["bytes_per_launch"],
         "achieved_GBps": kernels[dom]["GBps"],
