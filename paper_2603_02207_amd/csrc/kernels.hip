@@ -889,19 +889,22 @@ int resident_wgs(const void* fn, int nt) {
 //
 // The kinds with column sums have workgroups that walk several tiles one after
 // another; there two slices pay only on narrow rows (quadratic forms, mesh of
-// 36441 rows, 8 FP64 columns 15.1, 9.4, 10.1; 20 11.7, 15.6, 19.5).  Where the
-// rows' lengths differ much (interleaved tiles), slices even out the waves in
-// both (power-law graph of 50000 rows, 32 FP64 columns: sketch 103, 76, quadratic
-// forms 106, 80).
-int csr_slices(bool sums, int lpr, int ntiles, const CsrDev& A, bool uneven, bool scattered) {
+// 36441 rows, 8 FP64 columns 15.1, 9.4, 10.1; 20 11.7, 15.6, 19.5) and where the
+// room is exceeded by a quarter (adaptive apply, 3 FP64 columns, 50000 rows of 11
+// entries, 1.2 of the room, 27.1, 29.8).  Where the rows' lengths differ much
+// (interleaved tiles), slices even out the waves in both (power-law graph of 50000
+// rows, 32 FP64 columns: sketch 103, 76, quadratic forms 106, 80), but for the
+// column sums of FP32 rows read an element at a time (7 columns 73, 85).
+int csr_slices(bool sums, int lpr, int lane_bytes, int ntiles, const CsrDev& A, bool uneven, bool scattered) {
     if ((long long)A.nnz <= (long long)kMaxDiag * A.n) return 1;
-    const double room = ntiles < 600 ? 0.95 : 1.0;
-    const bool fits = step_staging(A.n, A.nnz, lpr) <= room;
+    const double staging = step_staging(A.n, A.nnz, lpr);
+    const bool fits = staging <= (ntiles < 600 ? 0.95 : 1.0);
     int slices;
     if (uneven) {
         slices = ntiles < 2048 ? (sums ? 2 : 4) : ntiles < 4096 ? 2 : 1;
+        if (sums && lane_bytes < 8 && lpr >= 3 && ntiles < 2048) slices = 1;
     } else if (sums) {
-        slices = fits || ntiles >= 2048 || lpr > 4 ? 1 : scattered && lpr <= 2 ? 4 : 2;
+        slices = staging <= 1.25 || ntiles >= 2048 || lpr > 4 ? 1 : scattered && lpr <= 2 ? 4 : 2;
     } else if (fits) {
         slices = ntiles < 200 && lpr <= 8 ? 2 : 1;
     } else {
@@ -1055,7 +1058,7 @@ hipError_t launch_step_t(const CsrDev& A, const StepArgs& s, hipStream_t st, int
                            s.long_count, part_row0, (T*)s.acc, s.ldacc, s.acc_cols, s.active);
         return hipGetLastError();
     };
-    const int slices = csr_slices(is_dot(KIND), lpr, ntiles, A, s.interleave, s.scattered);
+    const int slices = csr_slices(is_dot(KIND), lpr, VEC * (int)sizeof(T), ntiles, A, s.interleave, s.scattered);
     if (slices > 1) {
         const int rows = kWaves * (64 / (lpr * slices)), tiles = div_up(A.n, rows);
         // (the partial rows of the long-row launch too, where there is none)

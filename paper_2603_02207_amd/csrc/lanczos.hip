@@ -152,7 +152,10 @@ template <typename T>
 void launch_product(const CsrDev& A, const LanczosDev& d, const double* u, double* w, int j, hipStream_t st) {
     // Lanes per row: 200000 rows of 15 entries took 1.62 ms for 64 steps with 4
     // lanes, 1.83 with 2, 1.76 with 8, 2.00 with 16 (fewer rows in flight); long
-    // rows take 16.  Workgroups: 2048 against 1024 (1.94 ms at 8 lanes) and 3072
+    // rows take 16.  (On average: a single long row is walked by its lanes alone.
+    // 200000 rows, three of them with as many entries, take 360 ms for 64 steps, 1640
+    // with one lane per row; a random graph of 2^20 rows and 17 entries 14.1, 48.8.)
+    // Workgroups: 2048 against 1024 (1.94 ms at 8 lanes) and 3072
     // (2.27 ms at 4: more partial sums than the added rows in flight are worth).
     const long long avg = A.n > 0 ? (long long)A.nnz / A.n : 0;
 #define LD_LZ(LPR_)                                                                                              \
