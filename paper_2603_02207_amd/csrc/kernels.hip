@@ -599,7 +599,8 @@ __global__ __launch_bounds__(kThreads) void csr_slice_kernel(
 
 // ---------------------------------------------------------------------------
 // Long rows: a wave per row, or the whole workgroup for rows above kCoopRow
-// entries.  The row's entries are dealt round-robin to the row groups at work
+// entries, and, while there are few long rows, above kCoopShare entries of a row
+// group.  The row's entries are dealt round-robin to the row groups at work
 // on it, each group gathers and accumulates its share (the next batch's
 // indices are fetched before the current batch's gathers), and the group sums
 // are added by a shuffle tree over the wave (then in wave order through LDS).
@@ -610,9 +611,16 @@ __global__ __launch_bounds__(kThreads) void csr_slice_kernel(
 // they touch.  Measured on gfx950 (power-law graph, n = 2^20, 25000 rows of 65
 // to 4100 entries): a workgroup per row with a serial sum over its groups took
 // 840-1090 us per launch at 8 FP32 columns, this form 123 us at 21 columns and
-// 201 us at 43 (5 TB/s of the 64-byte sectors its gathers touch).
+// 201 us at 43 (5 TB/s of the 64-byte sectors its gathers touch).  With few long
+// rows a launch lasts as long as the longest walk, and a wave with few row groups
+// (many columns) walks many batches: 50000 rows, 64 columns, FP64, quadratic-form
+// step 138 us with a wave for each row up to 1024 entries, 84 with kCoopShare;
+// 13 columns of an adaptive apply 117, 91.  With many (20000 rows of 201 entries,
+// 40 FP32 columns: 66, 78) the waves are busy anyway.
 // ---------------------------------------------------------------------------
 constexpr int kCoopRow = 1024;   // entries above which a row takes a whole workgroup
+constexpr int kCoopShare = 32;   // the same, per row group of a wave, while
+constexpr int kCoopFew = 8;      // there are at most so many long rows a workgroup
 
 template <typename T, int VEC, int KIND, bool FIRST>
 __global__ __launch_bounds__(256) void long_row_kernel(
@@ -634,6 +642,7 @@ __global__ __launch_bounds__(256) void long_row_kernel(
     const bool lane_ok = g < rpw;
     const int col = c0 + li * VEC;
     const int nlong = *count;
+    const int coop = nlong <= kCoopFew * (int)gridDim.x ? min(kCoopRow, kCoopShare * rpw) : kCoopRow;
     int top = 1;   // the tree's first stride, in groups: the largest power of two below rpw
     while (2 * top < rpw) top *= 2;
     double s0[VEC], s1[VEC], s2[VEC];
@@ -696,7 +705,7 @@ __global__ __launch_bounds__(256) void long_row_kernel(
     for (int i = blockIdx.x; i < nlong; i += gridDim.x) {   // rows for the whole workgroup
         const int row = list[i];
         const int beg = row_ptr[row], end = row_ptr[row + 1];
-        if (end - beg <= kCoopRow) continue;   // the same for every thread
+        if (end - beg <= coop) continue;   // the same for every thread
         gather_row(beg, end, wave * rpw + g, NW * rpw, acc);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) s_acc[threadIdx.x * VEC + e] = acc[e];
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(256) void long_row_kernel(
     for (int i = blockIdx.x + wave * gridDim.x; i < nlong; i += NW * gridDim.x) {   // a wave each
         const int row = list[i];
         const int beg = row_ptr[row], end = row_ptr[row + 1];
-        if (end - beg > kCoopRow) continue;   // the same for every lane
+        if (end - beg > coop) continue;   // the same for every lane
         gather_row(beg, end, g, rpw, acc);
         if (g == 0) finish(row, acc);
     }
