@@ -64,7 +64,7 @@ CsrDev dev_of(const ld_csr* A) {
 
 // Workspace of the list of rows with more than kLongRow entries.
 size_t long_rows_bytes(const ld_csr* A) {
-    return align_up((size_t)A->n * 4) + align_up(((size_t)A->n / 256 + 4) * 4) + align_up(16);
+    return align_up((size_t)A->n * 4) + align_up(((size_t)A->n / 256 + 4) * 4);
 }
 
 // Workspace of the row probe and the diagonal storage (taken whether or not
@@ -672,7 +672,6 @@ int prepare_rows(const ld_csr* A, const ld_options& o, Arena& ar, hipStream_t st
         return fail(LD_EINVAL, "tile_order must be LD_TILES_AUTO, LD_TILES_XCD_BANDS or LD_TILES_INTERLEAVED");
     int* list = (int*)ar.take((size_t)A->n * 4);
     int* tmp = (int*)ar.take(((size_t)A->n / 256 + 4) * 4);
-    (void)ar.take(16);
     void* buf = o.csr_only ? nullptr : ar.take((size_t)A->n * kMaxDiag * (A->dtype == LD_F64 ? 8 : 4));
     uint16_t* pres = o.csr_only ? nullptr : (uint16_t*)ar.take((size_t)A->n * 2);
     int* info = (int*)ar.take(256);
@@ -1969,7 +1968,7 @@ size_t adaptive_ws_bytes(const ld_csr* A, int ncols, const ld_options& o, bool c
     return (chunked ? adaptive_chunks_bytes(adaptive_chunk_bytes(A, ncols, o), w) : 0) + 2 * w +
            align_up((size_t)step_num_wg_any(n) * 64 * 8) +
            align_up((size_t)cross_num_wg(n) * 64 * 64 * 8) + align_up(64 * 64 * 8) + align_up(256) +
-           align_up((size_t)ncols * 4) + align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+           align_up((size_t)ncols * 4) + long_rows_bytes(A) + dia_bytes(A, o);
 }
 
 // adaptive_fused's launches on qc columns, and whether their partial sums have
@@ -2371,7 +2370,7 @@ size_t packed_block_bytes(const ld_csr* A, int64_t ncols) {
 
 // Workspace besides the blocks: the matrix preparation.
 size_t apply_rest_bytes(const ld_csr* A, const ld_options& o) {
-    return align_up(256) + long_rows_bytes(A) + dia_bytes(A, o);
+    return long_rows_bytes(A) + dia_bytes(A, o);
 }
 
 // Workspace that no path of the call can do more with.
@@ -2555,7 +2554,6 @@ int ld_apply_log_adaptive(const ld_csr* A, double lmin, double lmax, int32_t max
     b.sums = (double*)ar.take(64 * 64 * 8);
     b.mask = (uint64_t*)ar.take(256);
     b.deg = (int*)ar.take((size_t)nc * 4);
-    (void)ar.take(256);
     LongRows lr;
     LD_CHECK(prepare_rows(A, o, ar, st, lr));
     const bool resident = resident_fits(A, lr, o, p.degree);

@@ -1,7 +1,7 @@
 """ld_logdet_estimate in a workspace without room for the single column block that scattered matrices take: it keeps
 the column blocks that follow the stored bytes, as the size of such a workspace (a constant of the shape below) was
 the entry point's whole requirement before that block was introduced.  The blocks group FP64 sums differently and
-nothing else: 1e-11.  One granule less is refused."""
+nothing else: 1e-11.  A page less is refused."""
 import ctypes
 
 import pytest
@@ -36,7 +36,7 @@ def test_smaller_workspace_keeps_several_blocks():
     need = ld.workspace_size(A, DEGREE, QUERIES)
     assert need > LEAST
     got = {}
-    for size in (need, LEAST, LEAST - 256):
+    for size in (need, LEAST, LEAST - 4096):
         ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         out, st = ctypes.c_double(0.0), nat.LdStats()
         rc = nat.load().ld_logdet_estimate(
