@@ -98,8 +98,10 @@ typedef struct {
                                 within 170 MB and, with the matrix as stored,
                                 within 240 MB (the Infinity Cache), else, and
                                 for a CSR matrix whose columns are scattered
-                                over the rows, one block of at most 64 columns
-                                (the gradient's blocks are always of that kind).  The blocks
+                                over the rows (where the workspace has room
+                                for it, and not in the adaptive estimate), one
+                                block of at most 64 columns (the gradient's
+                                blocks are always of that kind).  The blocks
                                 set how the quadratic forms' sums are
                                 grouped, hence their last bits              */
     int64_t taylor_cap;      /* max Taylor order of Alg. 1; 0 = 100000000      */
@@ -340,8 +342,9 @@ int ld_logdet_estimate_noalloc(const ld_csr* A, double lmin, double lmax, int32_
  * paper).  When the estimate takes the squared basis for its quadratic forms
  * (opts->dot_mode) and k + k_G <= 64, the forward vectors of the estimate's
  * own passes are kept and swept in reverse (the returned estimate is then
- * bit-identical to ld_logdet_estimate's where that takes one launch per step
- * and the same column blocks, else equal to rounding); otherwise one forward
+ * bit-identical to ld_logdet_estimate's where that takes one launch per step,
+ * as with any tile_order but auto, and the same column blocks, else equal to
+ * rounding); otherwise one forward
  * pass in the Newton form and one reverse sweep (estimates agree to rounding).  Vectors
  * are kept every opts->ckpt_stride steps (0: all of them while they fit
  * 64 GiB, else the smallest stride that does) and recomputed in between.

@@ -16,8 +16,11 @@
 // step (28.5-36 us at 20 FP32 columns and 1024^2 points, 6 TB/s from the
 // Infinity Cache); here it moves once per LV steps and the vector ALUs become
 // the bound: about 35 instructions per step and chunk, a third of them on the
-// lanes and lines two waves both walk (the table at fused_levels).  To that
-// end alpha is folded into the diagonals' values and alpha*centre - beta into
+// lanes and lines two waves both walk (the table at fused_levels).  By counters
+// they are busy for 73% of a launch of six sketch steps and 55% of one of three
+// quadratic-form steps (1024^2 points, 20 FP32 columns; 41% of four adaptive
+// steps at 2048^2); the rest is latency at 2.1 to 2.4 waves a SIMD in the mean
+// (3.9 at the start: they end at different times).  To that end alpha is folded into the diagonals' values and alpha*centre - beta into
 // one coefficient (both formed in FP64): five products per element, in the
 // order of the offsets, where the single steps take seven.  Two positions per
 // lane measured slower (17.9 against 15.6 us per step at four levels): half

@@ -69,7 +69,7 @@ struct StepArgs {
     double* ps2;
     int part_ld;
     // Rows with more than kLongRow entries, when listed here, are skipped by the
-    // row-group kernel and done by a workgroup each (partial rows after the
+    // row-group kernel and done by a launch of their own (partial rows after the
     // regular ones: kLongWgs of them).
     const int* long_rows;      // device list of long rows (ascending), or null
     const int* long_count;     // device count of the list
