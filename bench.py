@@ -532,12 +532,14 @@ def kernel_records(st):
 
 
 def step_bound(rec) -> str:
-    """What bounds a phase's launches.  Several steps in one: the vector ALUs (by counters busy for 73% of a sketch
-    launch and 55% of one of the quadratic forms at 1024^2 points, profiles/fused_kernel_grid1024_valu.md; the rest
-    is latency at 2.2 to 2.6 waves a SIMD), at any size: 5000^2 points take the same time per element.  All steps of
-    a small matrix in one: the LDS reads of a row's neighbours, one after another, and two barriers a step."""
+    """What bounds a phase's launches.  Several steps in one: in the Infinity Cache the vector ALUs (by counters busy
+    for 73% of a sketch launch and 55% of one of the quadratic forms at 1024^2 points,
+    profiles/fused_kernel_grid1024_valu.md; the rest is latency at 2.2 to 2.7 waves a SIMD); beyond it HBM, of whose
+    peak they reach a larger part than of the ALUs' (quadratic forms at 5000^2 points: 4.2 TB/s, 0.52, against 0.27;
+    the counters' bytes make 4.5 TB/s, a copy 4.7).  All steps of a small matrix in one: the LDS reads of a row's
+    neighbours, one after another, and two barriers a step."""
     if rec["kernel"] == "fused_kernel":
-        return "valu"
+        return "valu" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
     if rec["kernel"] == "resident_kernel":
         return "lds_latency"
     return "infinity_cache" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
@@ -554,7 +556,7 @@ def step_tflops(tag, rec, st, nnz) -> float:
 def roofline(tag, rec, st, nnz):
     """The rate of a phase's step kernel in the unit of what bounds it."""
     bound = step_bound(rec)
-    if rec["kernel"] in ("fused_kernel", "resident_kernel"):
+    if bound in ("valu", "lds_latency"):
         achieved, peak, unit = step_tflops(tag, rec, st, nnz), VALU_PEAK_TFLOPS, "TFLOP/s"
     else:
         achieved, peak, unit = rec["GBps"], HBM_PEAK_GBS, "GB/s"
@@ -565,8 +567,10 @@ def roofline(tag, rec, st, nnz):
 def working_set(rec) -> str:
     mb = f"{rec['bytes_per_launch'] / 1e6:.0f} MB per launch "
     if rec["kernel"] == "fused_kernel":
-        return mb + (f"of {rec['steps_per_launch']:.1f} steps: the block moves once per launch, so bytes do not bound "
-                     "it; peak: FP32 vector products without packed instructions")
+        mb += f"of {rec['steps_per_launch']:.1f} steps: the block moves once per launch, "
+        if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES:
+            return mb + "within the Infinity Cache; peak: FP32 vector products without packed instructions"
+        return mb + "from and to HBM"
     if rec["kernel"] == "resident_kernel":
         return mb + "of all steps, from and to LDS and registers"
     if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES:

@@ -9,11 +9,14 @@ STENCIL = {"ms_steps1": 0.86, "launches1": 14, "bytes1": 14 * 165e6, "ms_steps23
 SMALL = {"ms_steps1": 0.055, "launches1": 1, "bytes1": 1e5, "ms_steps23": 0.075, "launches23": 1, "bytes23": 1e5,
          "dia_diagonals": 5, "dia_constant": 1, "degree": 40, "k": 10, "k_G": 10, "block_cols1": 10,
          "block_cols23": 20, "dot_mode_used": 2, "n": 1024}
+LARGE = {**STENCIL, "ms_steps1": 10.9, "bytes1": 14 * 2004e6, "ms_steps23": 13.0, "launches23": 14,
+         "bytes23": 14 * 3907e6, "k": 10, "k_G": 10, "block_cols1": 10, "n": 25000000}   # beyond the Infinity Cache
 SINGLE = {**STENCIL, "launches1": 80, "launches23": 80, "block_cols23": 20, "dia_constant": 0}
 
 
 @pytest.mark.parametrize("st,name,bound,unit", [
     (STENCIL, "fused_kernel", "valu", "TFLOP/s"),
+    (LARGE, "fused_kernel", "hbm", "GB/s"),
     (SMALL, "resident_kernel", "lds_latency", "TFLOP/s"),
     ({**SMALL, "dia_diagonals": 0, "dia_constant": 0}, "resident_kernel", "lds_latency", "TFLOP/s"),
     (SINGLE, "step_kernel", "infinity_cache", "GB/s"),
