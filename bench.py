@@ -536,7 +536,7 @@ def step_bound(rec) -> str:
     for 73% of a sketch launch and 55% of one of the quadratic forms at 1024^2 points,
     profiles/fused_kernel_grid1024_valu.md; the rest is latency at 2.2 to 2.7 waves a SIMD); beyond it HBM, of whose
     peak they reach a larger part than of the ALUs' (quadratic forms at 5000^2 points: 4.2 TB/s, 0.52, against 0.27;
-    the counters' bytes make 4.5 TB/s, a copy 4.7).  All steps of a small matrix in one: the LDS reads of a row's
+    the counters' bytes make 4.5 TB/s, a copy 4.7 to 5.1).  All steps of a small matrix in one: the LDS reads of a row's
     neighbours, one after another, and two barriers a step."""
     if rec["kernel"] == "fused_kernel":
         return "valu" if rec["bytes_per_launch"] <= INFINITY_CACHE_BYTES else "hbm"
